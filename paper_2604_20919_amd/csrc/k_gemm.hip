@@ -9,26 +9,23 @@
 //     blocks of a 16-row group follow each other along k, so a wave-wide
 //     weight load reads 1 KB (or, for the 32x32 form, two 512-byte runs)
 //     contiguously;
-//   * two MFMA forms share that layout: 16x16x32 tiles (16 slots per tile)
-//     for small slot counts, where their finer slot padding wins, and
-//     32x32x16 tiles (32 slots per tile) above, where the form's higher
-//     rate (measured 2.1 vs 1.2 PFLOP/s) wins; every product runs twice, once
-//     per activation plane, so the MFMA rate matters even here;
+//   * two MFMA forms share that layout: 32x32x16 tiles (32 slots per tile,
+//     measured 2.1 PFLOP/s against 1.2 for the other; every product runs
+//     twice, once per activation plane, so the MFMA rate matters even here)
+//     and, for the products of small models, 16x16x32 tiles with smaller
+//     workgroups;
 //   * the activation chunk X[0:T][k0:k0+KC] is staged in LDS (double
 //     buffered) and read by all waves of the workgroup as the B operand;
 //     activations come as two bf16 planes (hi, lo = x - hi) that are
 //     multiplied separately, which carries them at about 16 significant bits;
-//   * software pipeline per chunk: the loads of X(c+1) are issued before the
-//     weight loads of chunk c+1, so storing X(c+1) to LDS after computing
-//     chunk c waits for X only and the weight prefetch stays in flight;
 //   * each wave owns a fixed set of weight rows and all T slots, so every
 //     weight byte is read once per call;
 //   * when there are too few column tiles to fill the GPU the k range is
 //     split over S workgroups; partial sums are written to a workspace and a
 //     second kernel (or a fused consumer) adds them in split order and
 //     applies the epilogue (no device-wide fences, deterministic results);
-//   * epilogues: fp32 store, residual add into the fp32 stream, or SwiGLU
-//     silu(g) * u with gate/up rows interleaved per 16-row group.
+//   * epilogues: fp32 store, SwiGLU silu(g) * u with gate/up rows interleaved
+//     per 16-row group, or the lm_head's softmax statistics.
 // An fp32 fallback (plain FMA loop) serves the fp32 model configuration.
 #include <algorithm>
 
@@ -82,10 +79,10 @@ struct GemmP {
     // the epilogue (sk_nwg = 0: off)
     // the piece waits for at most sk_polls polls of the count
     int sk_nwg, sk_maxp, sk_polls;
-    // column-split form at 225-240 slots: the last slot tile holds the hi
-    // rows of slots 224-239 in its rows 0-15 and their lo rows in rows 16-31
-    // (one tile-plane instead of two); 0: off
-    int pkl;
+    // slot groups (direct-staging form): a workgroup computes the MT slot
+    // tiles of one group; with more than one group, `tiles` row tiles make
+    // tiles * ng work tiles
+    int ng;
     int* sk_cnt;
     int32_t* flags;  // device error bits (bit 2: a stream-K wait gave up)
 };
@@ -105,12 +102,12 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // the workgroup's waves in wave order, i.e. in increasing vocab rows, and
 // leave as one 16-byte record per (workgroup, slot)
 template <int NTH, int NW, int NSLOT>
-__device__ __forceinline__ void lmstat_merge_waves(const GemmP& p, const VStat* stg, int wgi) {
-    for (int i = threadIdx.x; i < NSLOT && i < p.T; i += NTH) {
+__device__ __forceinline__ void lmstat_merge_waves(const GemmP& p, const VStat* stg, int wgi, int tb = 0) {
+    for (int i = threadIdx.x; i < NSLOT && tb + i < p.T; i += NTH) {
         VStat st = stg[i];
 #pragma unroll
         for (int w = 1; w < NW; ++w) st = vstat_merge(st, stg[w * NSLOT + i]);
-        p.lstat[(size_t)i * p.tiles + wgi] = st;
+        p.lstat[(size_t)(tb + i) * p.tiles + wgi] = st;
     }
 }
 
@@ -156,17 +153,8 @@ __device__ __forceinline__ float row_rstd(const GemmP& p, int t) {
 
 __device__ __forceinline__ float silu(float g) { return g / (1.0f + expf(-g)); }
 
-template <int EPI>
 __device__ __forceinline__ void epi_store4(const GemmP& p, int t, int col, f32x4 v, float sc) {
-    v *= sc;
-    float* o = (float*)p.out + (size_t)t * p.ldo + col;
-    if (EPI == EPI_RESID) {
-        f32x4 x = *(f32x4*)o;
-        x += v;
-        *(f32x4*)o = x;
-    } else {
-        *(f32x4*)o = v;
-    }
+    *(f32x4*)((float*)p.out + (size_t)t * p.ldo + col) = v * sc;
 }
 
 // SwiGLU output as the next GEMM's activation planes: hi = bf16(a) at out,
@@ -326,69 +314,27 @@ void k_gemm16(GemmP p) {
                 w[ks][s] = __builtin_bit_cast(
                     bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wres, woff[s], (c * KS + ks) * 1024, kWeightAux));
     };
-    // The X fragments of a group of slot tiles are read before their MFMAs
-    // (all tiles of the k-step up to 8 tiles, groups of 4 above), and every
-    // slot tile of the class is computed (tiles past T multiply clamped
+    // The X fragments of all slot tiles of a k-step are read before their
+    // MFMAs, and every slot tile of the class is computed (tiles past T multiply clamped
     // copies of row T-1 and are never stored): a per-tile branch would
     // serialise LDS latency and MFMAs tile by tile.
-    constexpr int MG = MT <= 8 ? MT : 4;
-    // all slot tiles' B fragments of one k-step
-    auto read_x = [&](bf16x8 (&xf)[PL][MT], const bf16_t* xb, int ks) {
-#pragma unroll
-        for (int pl = 0; pl < PL; ++pl)
-#pragma unroll
-            for (int g = 0; g < MT; ++g)
-                xf[pl][g] = *(const bf16x8*)(xb + pl * PLANE + (g * 16 + lr) * LDX + ks * 32 + 8 * lg);
-    };
     auto compute = [&](int buf, const bf16x8 (&w)[KS][NSUB]) {
         const bf16_t* xb = xs[buf];
-        if constexpr (MT <= 8 && NW == 8) {
-            // The next k-step's fragments are requested before this k-step's
-            // MFMAs (scheduling barriers keep the order), so the LDS latency
-            // hides under the matrix work instead of stalling each MFMA pair
-            // (gate/up at T = 80: 112 -> 102 us).  Eight-wave tiles only: the
-            // second fragment set would cost the four-wave tiles (lm_head)
-            // their second wave per SIMD.
-            bf16x8 xf[2][PL][MT];
-            read_x(xf[0], xb, 0);
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                if (ks + 1 < KS) read_x(xf[(ks + 1) & 1], xb, ks + 1);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int g = 0; g < MT; ++g)
-#pragma unroll
-                    for (int pl = 0; pl < PL; ++pl)
-#pragma unroll
-                        for (int s = 0; s < NSUB; ++s)
-                            acc[s][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][s], xf[ks & 1][pl][g],
-                                                                                acc[s][g], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            return;
-        }
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
+            bf16x8 xf[PL][MT];
 #pragma unroll
-            for (int m0 = 0; m0 < MT; m0 += MG) {
-                bf16x8 xf[PL][MG];
+            for (int pl = 0; pl < PL; ++pl)
+#pragma unroll
+                for (int g = 0; g < MT; ++g)
+                    xf[pl][g] = *(const bf16x8*)(xb + pl * PLANE + (g * 16 + lr) * LDX + ks * 32 + 8 * lg);
+#pragma unroll
+            for (int g = 0; g < MT; ++g)
 #pragma unroll
                 for (int pl = 0; pl < PL; ++pl)
 #pragma unroll
-                    for (int g = 0; g < MG; ++g)
-                        if (m0 + g < MT)
-                            xf[pl][g] = *(const bf16x8*)(xb + pl * PLANE + ((m0 + g) * 16 + lr) * LDX +
-                                                         ks * 32 + 8 * lg);
-#pragma unroll
-                for (int g = 0; g < MG; ++g)
-                    if (m0 + g < MT)
-#pragma unroll
-                        for (int pl = 0; pl < PL; ++pl)
-#pragma unroll
-                            for (int s = 0; s < NSUB; ++s)
-                                acc[s][m0 + g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                    w[ks][s], xf[pl][g], acc[s][m0 + g], 0, 0, 0);
-            }
+                    for (int s = 0; s < NSUB; ++s)
+                        acc[s][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][s], xf[pl][g], acc[s][g], 0, 0, 0);
         }
     };
 
@@ -550,97 +496,134 @@ void k_gemm16(GemmP p) {
         } else {
 #pragma unroll
             for (int s = 0; s < NSUB; ++s)
-                epi_store4<EPI>(p, t, (unit * NSUB + s) * 16 + 4 * lg, acc[s][m], sc);
+                epi_store4(p, t, (unit * NSUB + s) * 16 + 4 * lg, acc[s][m], sc);
         }
     }
 }
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// 32x32x16 form.  MT: 32-slot tiles; NS: 32-row weight groups (pairs of
-// 16-row groups) per wave; KC: k per chunk (a multiple of 16); NW: waves per
-// workgroup; PL: activation planes; PD: chunks of prefetch.
-// PK (two planes packed, for 32a < T <= 32a + 16): the B operand's columns
-// are (slot, plane) pairs instead of slots, MT = 2a + 1 tiles in one staged
-// plane: tiles 0..a-1 the hi plane of slots 0..32a-1, tile a the hi plane of
-// slots 32a.. in columns 0-15 and their lo plane in columns 16-31, tiles
-// a+1..2a the lo plane of slots 0..32a-1.  That is one tile fewer than two
-// planes of a + 1 tiles each; the epilogue adds each slot's hi and lo sums
-// (same lane of tiles m and m + a + 1, or lanes l and l ^ 16 of tile a).
-//
-// CS (column split): CS waves share one row unit and each multiplies MT/CS
-// of the slot tiles.  With NS = 2 (64 weight rows per wave) every B
-// fragment read from LDS then feeds two MFMAs instead of one: four SIMDs
-// issuing 32-cycle MFMAs ask for 64 bytes per clock of LDS reads instead
-// of 128, at the same accumulator count per wave.
-// SKF: stream-K (unsplit column-split GEMMs, see GemmP).
-template <int MT, int NS, int KC, int EPI, bool SPLIT, int NW, int PL, int PD, bool PK = false, int CS = 1,
-          bool SKF = false>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW > 8 ? NW / 4 : 1, NW > 8 ? NW / 4 : 2)))
+// Direct-staging form: the B fragments of N consecutive slot tiles (4 KB
+// apart) requested from LDS without a wait, and the wait that leaves at most
+// LEFT later requests in flight; the waits take the fragments as operands, so
+// nothing that uses them is scheduled before.
+template <int N>
+__device__ __forceinline__ void lds_read_tiles(bf16x8 (&f)[N], uint32_t a) {
+    if constexpr (N == 1) asm volatile("ds_read_b128 %0, %1" : "=&v"(f[0]) : "v"(a) : "memory");
+    if constexpr (N == 2)
+        asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:4096"
+                     : "=&v"(f[0]), "=&v"(f[1]) : "v"(a) : "memory");
+    if constexpr (N == 3)
+        asm volatile("ds_read_b128 %0, %3\n\tds_read_b128 %1, %3 offset:4096\n\tds_read_b128 %2, %3 offset:8192"
+                     : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]) : "v"(a) : "memory");
+    static_assert(N >= 1 && N <= 6, "tiles per wave");
+    if constexpr (N == 4)
+        asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:4096\n\tds_read_b128 %2, %4 offset:8192\n\t"
+                     "ds_read_b128 %3, %4 offset:12288"
+                     : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]) : "v"(a) : "memory");
+    if constexpr (N == 5)
+        asm volatile("ds_read_b128 %0, %5\n\tds_read_b128 %1, %5 offset:4096\n\tds_read_b128 %2, %5 offset:8192\n\t"
+                     "ds_read_b128 %3, %5 offset:12288\n\tds_read_b128 %4, %5 offset:16384"
+                     : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]) : "v"(a) : "memory");
+    if constexpr (N == 6)
+        asm volatile("ds_read_b128 %0, %6\n\tds_read_b128 %1, %6 offset:4096\n\tds_read_b128 %2, %6 offset:8192\n\t"
+                     "ds_read_b128 %3, %6 offset:12288\n\tds_read_b128 %4, %6 offset:16384\n\t"
+                     "ds_read_b128 %5, %6 offset:20480"
+                     : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]), "=&v"(f[5])
+                     : "v"(a) : "memory");
+}
+template <int LEFT, int N>
+__device__ __forceinline__ void lds_wait_tiles(bf16x8 (&f)[N]) {
+    if constexpr (N == 1) asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(f[0]) : "n"(LEFT));
+    if constexpr (N == 2) asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(f[0]), "+v"(f[1]) : "n"(LEFT));
+    if constexpr (N == 3) asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]) : "n"(LEFT));
+    if constexpr (N == 4)
+        asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]) : "n"(LEFT));
+    if constexpr (N == 5)
+        asm volatile("s_waitcnt lgkmcnt(%5)"
+                     : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]) : "n"(LEFT));
+    if constexpr (N == 6)
+        asm volatile("s_waitcnt lgkmcnt(%6)"
+                     : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]), "+v"(f[5]) : "n"(LEFT));
+}
+
+// 32x32x16 form.  MT: 32-slot tiles of a workgroup; a wave multiplies 64
+// weight rows (two 32-row groups), so every B fragment read from LDS feeds two
+// MFMAs: four SIMDs issuing 32-cycle MFMAs then ask for 64 bytes per clock of
+// LDS reads instead of 128.
+// CS = 1, four waves (up to six tiles, one set of accumulators per wave; up
+// to four tiles two workgroups share a CU); CS = 2 (column split), eight
+// waves: two waves share one row unit and each multiplies MT/2 of the tiles.
+// Both hold 256 weight rows per workgroup.
+// Slot groups (ng > 1): workgroups b and b + 8 (the same XCD, dispatched
+// together) compute the same weight rows for consecutive groups of MT tiles,
+// so the second finds the weights in its XCD's L2.
+// SKF: stream-K (unsplit products, see GemmP).
+template <int MT, int EPI, bool SPLIT, int NW, int CS, bool SKF = false>
+__global__ __launch_bounds__(64 * NW)
+__attribute__((amdgpu_waves_per_eu(1, CS == 2 ? 2 : MT >= 5 ? 1 : MT >= 3 ? 2 : 4)))
 void k_gemm32(GemmP p) {
-    static_assert(!PK || (PL == 2 && MT % 2 == 1), "packed planes: two planes, 2a + 1 tiles");
-    static_assert(MT % CS == 0 && NW % CS == 0 && (CS == 1 || !PK),
-                  "column split: whole tiles per wave, no packed planes");
-    static_assert(!SKF || (CS > 1 && !SPLIT && EPI == EPI_SWIGLU), "stream-K: the unsplit SwiGLU product");
+    constexpr int PL = 2;                // activation planes
+    constexpr int NS = 2;                // 32-row groups per wave
+    constexpr int KC = 64;               // k per chunk
+    static_assert(MT % CS == 0 && NW == 4 * CS, "whole tiles per wave, 256 weight rows per workgroup");
+    static_assert(!SKF || (!SPLIT && EPI == EPI_SWIGLU), "stream-K: the unsplit SwiGLU product");
     constexpr int MTW = MT / CS;         // slot tiles per wave
-    constexpr int PLS = PK ? 1 : PL;     // staged (and multiplied) planes
-    constexpr int PA = MT / 2;           // packed: full tiles per plane
     constexpr int NTH = 64 * NW;         // threads per workgroup
-    constexpr int ROWS_PER_TILE = 32;
     constexpr int KS = KC / 16;          // MFMA k-steps per chunk
-    constexpr int LDX = KC + 8;          // padded LDS row (bf16 elements)
-    constexpr int PPR = KC / 8;          // 16-byte pieces per staged row
-    constexpr int NPP = MT * 32 * PPR;   // pieces per staged plane
-    constexpr int NPC = PLS * NPP;       // pieces per staged chunk (all planes)
-    constexpr int XPT = (NPC + NTH - 1) / NTH;  // X pieces per thread
-    constexpr bool XEVEN = NPC % NTH == 0;
-    constexpr int PLANE = MT * 32 * LDX;  // LDS elements per plane
-    // NXB X staging buffers of XBUF elements (padded rows; the column-split
-    // form keeps two unpadded chunks in the same array); the split epilogue
-    // stages its partial sums in the same memory, which may need more
-    constexpr int XBUF = PLS * PLANE;
-    constexpr int NXB = 2;
-    constexpr int STG_BYTES = SPLIT ? CS * 32 * (NW / CS * NS * 32 + 4) * 4 : 0;
-    constexpr int XS_ELEMS = 2 * NXB * XBUF >= STG_BYTES ? NXB * XBUF : STG_BYTES / 2;
+    // weight register sets: two, except where the registers hold only one
+    constexpr int WD = MT == 8 ? 1 : 2;
+    // two X buffers of XBUF elements; the split epilogue stages its partial
+    // sums in the same memory, which may need more
+    constexpr int XBUF = PL * MT * 32 * KC;
+    constexpr int STG_BYTES = SPLIT ? CS * 32 * (NW / CS * NS * 32 + 4) * 4 : EPI == EPI_LMSTAT ? NW / CS * MT * 32 * 16 : 0;
+    constexpr int XS_ELEMS = 4 * XBUF >= STG_BYTES ? 2 * XBUF : STG_BYTES / 2;
     static_assert(XS_ELEMS * 2 <= 160 * 1024, "staging exceeds LDS");
     __shared__ __attribute__((aligned(16))) bf16_t xs[XS_ELEMS];
-    __shared__ float rsl[SPLIT ? 1 : MT * ROWS_PER_TILE];  // per-slot RMSNorm factor
+    __shared__ float rsl[SPLIT ? 1 : MT * 32];  // per-slot RMSNorm factor
 
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int lc = lane & 31, lh = lane >> 5;
-    // Stream-K: the workgroup's range of (row tile, chunk) pairs is shorter
-    // than a tile, so it is one piece of a tile or two: the head of the last
-    // tile and the tail of the first, taken in that order (k increasing, so
-    // all workgroups walk the activation chunks nearly together and share
-    // them in L2).  Otherwise one piece: the whole k range of a split.
-    int sk_np = 1, sk_t[2] = {0, 0}, sk_b[2] = {0, 0}, sk_e[2] = {0, 0};
+    // Work tile of this workgroup: (row tile, k split), for one slot group.
+    int bid = blockIdx.x, grp = 0;
+    if (!SKF && p.ng > 1) {
+        grp = (bid >> 3) % p.ng;
+        bid = (bid >> 3) / p.ng * 8 + (bid & 7);
+        if (bid >= p.tiles * p.S) return;  // the grid is rounded up to 8 workgroups per group
+    }
+    // Stream-K: the workgroup's range of (work tile, chunk) pairs is cut at
+    // the tile ends into pieces.  The piece of the last tile is taken first
+    // (when it does not end its tile, another workgroup waits for it), then
+    // the others in order.  Otherwise one piece: the whole k range of a split.
+    int sk_np = 1, sk_wb = 0, sk_we = 0, sk_t0 = 0;
     if constexpr (SKF) {
-        const int total = p.tiles * p.kchunks;
-        const int wb = sk_begin(blockIdx.x, total, p.sk_nwg), we = sk_begin(blockIdx.x + 1, total, p.sk_nwg);
-        const int t0 = wb / p.kchunks, t1 = (we - 1) / p.kchunks;
-        if (t0 == t1) {
-            sk_t[0] = t0; sk_b[0] = wb - t0 * p.kchunks; sk_e[0] = we - t0 * p.kchunks;
-        } else {
-            sk_np = 2;
-            sk_t[0] = t1; sk_b[0] = 0; sk_e[0] = we - t1 * p.kchunks;
-            sk_t[1] = t0; sk_b[1] = wb - t0 * p.kchunks; sk_e[1] = p.kchunks;
-        }
+        const int total = p.tiles * p.ng * p.kchunks;
+        sk_wb = sk_begin(blockIdx.x, total, p.sk_nwg);
+        sk_we = sk_begin(blockIdx.x + 1, total, p.sk_nwg);
+        sk_t0 = sk_wb / p.kchunks;
+        sk_np = (sk_we - 1) / p.kchunks - sk_t0 + 1;
     }
     for (int piece = 0; piece < sk_np; ++piece) {
-    const int split = SPLIT ? blockIdx.x % p.S : 0;
-    const int wgi = SKF ? (piece == 0 ? sk_t[0] : sk_t[1]) : (SPLIT ? blockIdx.x / p.S : blockIdx.x);
+    // the last piece's epilogue reads the row factors this one overwrites
+    if (SKF && piece > 0) __syncthreads();
+    const int split = SPLIT ? bid % p.S : 0;
+    // SKF: work tile (row tile, group), groups of a row tile consecutive
+    const int skt = SKF ? sk_t0 + (piece == 0 ? sk_np - 1 : piece - 1) : 0;
+    const int wgi = SKF ? skt / p.ng : (SPLIT ? bid / p.S : bid);
+    if constexpr (SKF) grp = skt % p.ng;
+    const int tb = grp * MT * 32;  // first slot of the group
 
     // Buffer resources: one uniform resource per operand, fixed 32-bit
     // per-lane offsets, uniform chunk offsets.  Out-of-range reads return 0
     // (and fetch nothing: a wave without a unit points past the buffer).
     const int wv = __builtin_amdgcn_readfirstlane(wave);
     const int half = CS == 1 ? 0 : wv % CS;   // which MT/CS slot tiles
+    const int wrow = wv / CS;                 // row unit within the workgroup
     const int m0 = half * MTW;
-    const int unit = wgi * p.G / p.WPS + wv / CS;
+    const int unit = wgi * p.G / p.WPS + wrow;
     const bool has_unit = unit < (wgi + 1) * p.G / p.WPS;
     const uint64_t wbytes = (uint64_t)p.vcols * (uint64_t)p.K * 2u;
-    const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)p.Wp, (short)0, (int)(wbytes > 0x7fffffffu ? 0x7fffffffu : wbytes), 0x00020000);
+    const int wrec = (int)(wbytes > 0x7fffffffu ? 0x7fffffffu : wbytes), xrec = PL * p.T * p.K * 2;
     // The A operand of a 16-k step (lane l: row l % 32, k 8*(l/32)..+7)
     // taken from the 16-row fragments: rows 0-15 / 16-31 are 16-row groups
     // 2g / 2g+1; k-step j sits in fragment j/2 at k 16*(j%2), i.e. lane slot
@@ -653,8 +636,6 @@ void k_gemm32(GemmP p) {
         woff[s] = has_unit ? g16 * (uint32_t)p.KT * 1024u + (uint32_t)((lane & 15) + 16 * lh) * 16u
                            : 0x80000000u;
     }
-    const __amdgpu_buffer_rsrc_t xres =
-        __builtin_amdgcn_make_buffer_rsrc((void*)p.X, (short)0, PL * p.T * p.K * 2, 0x00020000);
 
     f32x16 acc[NS][MTW];
 #pragma unroll
@@ -664,113 +645,105 @@ void k_gemm32(GemmP p) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[s][m][e] = 0.f;
 
-    const int c_begin = SKF ? (piece == 0 ? sk_b[0] : sk_b[1]) : split * p.kchunks / p.S;
-    const int c_end = SKF ? (piece == 0 ? sk_e[0] : sk_e[1]) : (split + 1) * p.kchunks / p.S;
-
-    // Register-ring pipeline with prefetch distance PD chunks (the form
-    // without column split; the column-split form below stages X by direct
-    // loads): while chunk c is multiplied (X from LDS buffer c&1, W from
-    // ring set c % NB), X and W of chunk c+PD are requested into ring set
-    // (c+PD) % NB, and X(c+1), requested PD-1 chunks earlier, is stored to
-    // the other LDS buffer.  The
-    // loop is unrolled by NB so that ring indices are compile-time constants
-    // (register copies would force waits on loads still in flight), the
-    // loads are unconditional (the chunk index is clamped; the last steps
-    // re-read a cached chunk) and scheduling barriers keep the order issue
-    // loads -> multiply -> store X.  X rows >= T are read as row T-1: they
-    // only feed output slots >= T, which are never stored.
-    constexpr int NB = PD + 1;
-    uint4 xr[NB][XPT];
-    bf16x8 wr[NB][KS][NS];
-    uint32_t xoff[XPT];
-#pragma unroll
-    for (int i = 0; i < XPT; ++i) {
-        const int idx = min((int)threadIdx.x + i * NTH, NPC - 1);
-        int pl = idx / NPP, row = (idx % NPP) / PPR;
-        const int cc = idx % PPR;
-        if (PK) {
-            // staged row -> (plane, slot) of the packed layout
-            const int v = row;
-            pl = v < 32 * PA + 16 ? 0 : 1;
-            row = v < 32 * PA + 16 ? v : v < 32 * PA + 32 ? v - 16 : v - 32 * (PA + 1);
-        }
-        const int r = min(row, p.T - 1);
-        xoff[i] = (((uint32_t)pl * (uint32_t)p.T + (uint32_t)r) * (uint32_t)p.K + (uint32_t)cc * 8u) * 2u;
-    }
-    auto load_x = [&](uint4 (&x)[XPT], int c) {
-        const int so = c * KC * 2;
-#pragma unroll
-        for (int i = 0; i < XPT; ++i)
-            x[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xres, xoff[i], so, kActAux));
-    };
-    auto store_x = [&](const uint4 (&x)[XPT], int buf) {
-#pragma unroll
-        for (int i = 0; i < XPT; ++i) {
-            const int idx = threadIdx.x + i * NTH;
-            const int pl = idx / NPP, pi = idx % NPP;
-            if (XEVEN || idx < NPC)
-                *(uint4*)(&xs[buf * XBUF + pl * PLANE + (pi / PPR) * LDX + (pi % PPR) * 8]) = x[i];
-        }
-    };
-    auto load_w = [&](bf16x8 (&w)[KS][NS], int c) {
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-            for (int s = 0; s < NS; ++s)
-                w[ks][s] = __builtin_bit_cast(
-                    bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wres, woff[s], (c * KS + ks) * 512, kWeightAux));
-    };
-    // The B fragments of a k-step (lane l: slot l % 32 of the tile, k
-    // 8*(l/32)..+7) are read for all tiles before their MFMAs, one k-step
-    // ahead, and every slot tile of the class is computed (tiles past T
-    // multiply clamped copies of row T-1 and are never stored).  MFMAs on one
-    // accumulator are MT*NS instructions apart (planes outermost).
-    auto read_x = [&](bf16x8 (&xf)[PLS][MT], const bf16_t* xb, int ks) {
-#pragma unroll
-        for (int pl = 0; pl < PLS; ++pl)
-#pragma unroll
-            for (int m = 0; m < MT; ++m)
-                xf[pl][m] = *(const bf16x8*)(xb + pl * PLANE + (m * 32 + lc) * LDX + ks * 16 + 8 * lh);
-    };
-    auto compute = [&](int buf, const bf16x8 (&w)[KS][NS]) {
-        if constexpr (CS == 1) {
-            const bf16_t* xb = xs + buf * XBUF;
-            bf16x8 xf[2][PLS][MT];
-            read_x(xf[0], xb, 0);
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                if (ks + 1 < KS) read_x(xf[(ks + 1) & 1], xb, ks + 1);
-#pragma unroll
-                for (int pl = 0; pl < PLS; ++pl)
-#pragma unroll
-                    for (int m = 0; m < MT; ++m)
-#pragma unroll
-                        for (int s = 0; s < NS; ++s)
-                            acc[s][m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[ks][s], xf[ks & 1][pl][m],
-                                                                                 acc[s][m], 0, 0, 0);
-            }
-        }
-    };
-
+    const int c_begin = SKF ? max(sk_wb - skt * p.kchunks, 0) : split * p.kchunks / p.S;
+    const int c_end = SKF ? min(sk_we - skt * p.kchunks, p.kchunks) : (split + 1) * p.kchunks / p.S;
     const int c_last = c_end - 1;
     // RMSNorm row factors of the tile's slots (epilogues that scale by
     // them): loads issued ahead of the pipeline prologue, the factors go to
     // LDS before the first barrier
-    constexpr int NSL = MT * ROWS_PER_TILE;
+    constexpr int NSL = MT * 32;
     constexpr int NSPT = SPLIT ? 1 : (NSL + NTH - 1) / NTH;  // slots per thread
     float ssv[NSPT][kNormKMax / kNormBlock];
     if constexpr (!SPLIT) {
 #pragma unroll
         for (int i = 0; i < NSPT; ++i) {
             const int sl = threadIdx.x + i * NTH;
-            load_row_ss(p, min(sl, p.T - 1), p.nss != nullptr && sl < NSL, ssv[i]);
+            load_row_ss(p, min(tb + sl, p.T - 1), p.nss != nullptr && sl < NSL, ssv[i]);
         }
     }
+    // Packed last tile (when the group's last tile holds at most 16 slots):
+    // its rows 0-15 hold their hi plane and rows 16-31 their lo plane, one
+    // tile-plane instead of two; the wave that holds it multiplies it in the
+    // plane-0 phases only
+    const int last_n = p.T - tb - (MT - 1) * 32;
+    const bool pkl = last_n > 0 && last_n <= 16;
+    const bool pkl_half = pkl && half == CS - 1;
+
+    // Two X buffers in LDS, WD weight register sets.  Per chunk c: the direct
+    // loads of X(c + 1) into the buffer that chunk c - 1 has left are issued
+    // first; phases (k-step, plane) follow, the next phase's fragments
+    // requested before this phase's NS * MTW MFMAs; after the last plane of a
+    // k-step its weight registers are reloaded with the same k-step of chunk
+    // c + WD; the wave then waits for its direct loads of chunk c + 1 and the
+    // barrier publishes the buffer.  Chunks past the range are requested from
+    // an empty buffer resource, so that nothing is fetched (re-reading the
+    // last chunk instead cost a tenth of a ten-chunk split's traffic) and the
+    // count of loads in flight stays the same for every chunk.  Three or four
+    // buffers and register sets measured the same or slower (T = 16: 3446 us
+    // a pass of 16 layers with two, 3503 / 3529 with three / four; T = 80:
+    // 4843, 4894 / 5025).
+    constexpr int NPH = KS * PL;
+    // X is staged by direct global-to-LDS loads: a chunk is MT * 8 blocks
+    // of 1 KB, block (plane, tile, row group of 8) holding 8 rows of 64 k
+    // (128 B each) whose 16-byte pieces are XOR-swizzled by the row
+    // (piece q at position q ^ ((row >> 1) & 7), row within the tile), so
+    // that the fragment reads of 16 rows hit 16 different bank groups.
+    // A wave's direct load fills one block (lane l: row l / 8, position
+    // l % 8), so each lane fetches the piece that belongs to its
+    // position; each wave loads MT * 8 / NW blocks per chunk.  Slots >= T are
+    // read as slot T-1: they only feed outputs that are never stored.
+    constexpr int NBK = MT * 8 / NW;
+    typedef __attribute__((address_space(3))) void lds_void;
+    uint32_t doff[NBK];
 #pragma unroll
-    for (int u = 0; u < PD; ++u) {
-        if constexpr (CS == 1) load_x(xr[u], min(c_begin + u, c_last));
-        load_w(wr[u], min(c_begin + u, c_last));
+    for (int i = 0; i < NBK; ++i) {
+        const int blk = wv * NBK + i, pl = blk / (MT * 4), mt = (blk >> 2) % MT, rb = blk & 3;
+        const int lrow = rb * 8 + (lane >> 3);
+        const int pc = (lane & 7) ^ ((lrow >> 1) & 7);
+        // packed last tile: rows 0-15 from the hi plane, 16-31 from the lo
+        // plane, of the same 16 slots
+        const bool pk = pkl && pl == 0 && mt == MT - 1;
+        const int spl = pk ? lrow >> 4 : pl;
+        const int row = min(tb + mt * 32 + (pk ? lrow & 15 : lrow), p.T - 1);
+        doff[i] = (((uint32_t)spl * (uint32_t)p.T + (uint32_t)row) * (uint32_t)p.K + (uint32_t)pc * 8u) * 2u;
     }
+    auto dma_x = [&](int c, int buf) {
+        const __amdgpu_buffer_rsrc_t xres =
+            __builtin_amdgcn_make_buffer_rsrc((void*)p.X, (short)0, c < c_end ? xrec : 0, 0x00020000);
+        bf16_t* base = xs + buf * XBUF + wv * NBK * 512;
+#pragma unroll
+        for (int i = 0; i < NBK; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(xres, (lds_void*)(base + i * 512), 16, (int)doff[i],
+                                                     c * KC * 2, 0, kActAux);
+    };
+    // fragment reads in inline assembly: the compiler cannot tell them from
+    // the direct loads into the other buffer and would wait for every
+    // load in flight before them; their completion is waited for
+    // explicitly, with the fragments as operands
+    const uint32_t xs_addr = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) bf16_t*)xs;
+    uint32_t loff[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+        loff[ks] = (uint32_t)((lc >> 3) * 1024 + (lc & 7) * 128 + (((2 * ks + lh) ^ ((lc >> 1) & 7)) * 16));
+    bf16x8 xq[2][MTW];
+    auto read_phase = [&](bf16x8 (&xf)[MTW], int buf, int ph) {
+        const int ks = ph / PL, pl = ph % PL;
+        lds_read_tiles(xf, xs_addr + (uint32_t)(buf * XBUF * 2) + loff[ks] + (uint32_t)((pl * MT + m0) * 4096));
+    };
+    bf16x8 wr[WD][KS][NS];
+    auto load_w_ks = [&](bf16x8 (&w)[NS], int c, int ks) {
+        const __amdgpu_buffer_rsrc_t wres =
+            __builtin_amdgcn_make_buffer_rsrc((void*)p.Wp, (short)0, c < c_end ? wrec : 0, 0x00020000);
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            w[s] = __builtin_bit_cast(
+                bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wres, woff[s], (c * KS + ks) * 512, kWeightAux));
+    };
+    dma_x(c_begin, 0);
+#pragma unroll
+    for (int u = 0; u < WD; ++u)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) load_w_ks(wr[u][ks], c_begin + u, ks);
     if constexpr (!SPLIT) {
 #pragma unroll
         for (int i = 0; i < NSPT; ++i) {
@@ -778,130 +751,40 @@ void k_gemm32(GemmP p) {
             if (sl < NSL) rsl[sl] = p.nss != nullptr ? rstd_of(p, ssv[i]) : 1.0f;
         }
     }
-    if constexpr (CS > 1) {
-        // Two X buffers; per chunk c: the direct loads of X(c + 1) into the
-        // other buffer are issued first; phases (k-step, plane) follow, the
-        // next phase's fragments requested before this phase's NS * MTW
-        // MFMAs; after the last plane of a k-step its weight registers are
-        // reloaded with the same k-step of chunk c + 1 (one register set,
-        // each fragment requested about a chunk ahead); the wave then waits
-        // for its direct loads and the barrier publishes the buffer.
-        constexpr int NPH = KS * PLS;
-        static_assert(NPH % 2 == 0, "phase fragments alternate between two register sets");
-        // X is staged by direct global-to-LDS loads: a chunk is 64 blocks of
-        // 1 KB, block (plane, tile, row group of 8) holding 8 rows of 64 k
-        // (128 B each) whose 16-byte pieces are XOR-swizzled by the row
-        // (piece q at position q ^ ((row >> 1) & 7), row within the tile), so
-        // that the fragment reads of 16 rows hit 16 different bank groups.
-        // A wave's direct load fills one block (lane l: row l / 8, position
-        // l % 8), so each lane fetches the piece that belongs to its
-        // position; each wave loads eight blocks per chunk.
-        static_assert(MT == 8 && KC == 64 && PLS == 2 && NW == 8 && MTW == 4,
-                      "direct X staging: 64 blocks per chunk, 8 per wave");
-        constexpr int DBUF = PLS * MT * 32 * KC;  // bf16 elements per staged chunk
-        static_assert(2 * DBUF <= XS_ELEMS, "two staged chunks fit the staging array");
-        typedef __attribute__((address_space(3))) void lds_void;
-        uint32_t doff[8];
+    // When a chunk starts its X has landed, and the weight loads issued after
+    // those direct loads may be in flight (loads retire in order).
+    wait_vm<WD * NS * KS, true>();  // and the row factors
+    barrier_nofence();
+    read_phase(xq[0], 0, 0);
+    for (int c0 = c_begin; c0 < c_end; c0 += 2) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int blk = wv * 8 + i, pl = blk >> 5, mt = (blk >> 2) & 7, rb = blk & 3;
-            const int lrow = rb * 8 + (lane >> 3);
-            const int pc = (lane & 7) ^ ((lrow >> 1) & 7);
-            // packed last tile: rows 0-15 from the hi plane, 16-31 from the lo
-            // plane, of the same 16 slots
-            const bool pk = p.pkl && pl == 0 && mt == MT - 1;
-            const int spl = pk ? lrow >> 4 : pl;
-            const int row = min(mt * 32 + (pk ? lrow & 15 : lrow), p.T - 1);
-            doff[i] = (((uint32_t)spl * (uint32_t)p.T + (uint32_t)row) * (uint32_t)p.K + (uint32_t)pc * 8u) * 2u;
-        }
-        auto dma_x = [&](int c, int buf) {
-            bf16_t* base = xs + buf * DBUF + wv * 8 * 512;
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(xres, (lds_void*)(base + i * 512), 16, (int)doff[i],
-                                                         c * KC * 2, 0, kActAux);
-        };
-        // fragment reads in inline assembly: the compiler cannot tell them from
-        // the direct loads into the other buffer and would wait for every
-        // load in flight before them; their completion is waited for
-        // explicitly, with the fragments as operands
-        const uint32_t xs_addr = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) bf16_t*)xs;
-        const bool pkl_half = p.pkl && half == CS - 1;  // this wave holds the packed tile
-        uint32_t loff[KS];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            loff[ks] = (uint32_t)((lc >> 3) * 1024 + (lc & 7) * 128 + (((2 * ks + lh) ^ ((lc >> 1) & 7)) * 16));
-        bf16x8 xq[2][MTW];
-        auto read_phase = [&](bf16x8 (&xf)[MTW], int buf, int ph) {
-            const int ks = ph / PLS, pl = ph % PLS;
-            const uint32_t a = xs_addr + (uint32_t)(buf * DBUF * 2) + loff[ks] + (uint32_t)((pl * MT + m0) * 4096);
-            asm volatile(
-                "ds_read_b128 %0, %4\n\t"
-                "ds_read_b128 %1, %4 offset:4096\n\t"
-                "ds_read_b128 %2, %4 offset:8192\n\t"
-                "ds_read_b128 %3, %4 offset:12288"
-                : "=&v"(xf[0]), "=&v"(xf[1]), "=&v"(xf[2]), "=&v"(xf[3])
-                : "v"(a)
-                : "memory");
-        };
-        auto load_w_ks = [&](bf16x8 (&w)[NS], int c, int ks) {
-#pragma unroll
-            for (int s = 0; s < NS; ++s)
-                w[s] = __builtin_bit_cast(
-                    bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wres, woff[s], (c * KS + ks) * 512, kWeightAux));
-        };
-        dma_x(c_begin, 0);
-        __syncthreads();
-        read_phase(xq[0], 0, 0);
-        for (int c = c_begin; c < c_end; ++c) {
-            const int b = (c - c_begin) & 1;
-            const int cn = min(c + 1, c_last);
-            dma_x(cn, b ^ 1);
+        for (int u = 0; u < 2; ++u) {
+            const int c = c0 + u;
+            if (c >= c_end) break;
+            dma_x(c + 1, u ^ 1);
 #pragma unroll
             for (int ph = 0; ph < NPH; ++ph) {
                 if (ph + 1 < NPH) {
-                    read_phase(xq[(ph + 1) & 1], b, ph + 1);
-                    asm volatile("s_waitcnt lgkmcnt(4)"
-                                 : "+v"(xq[ph & 1][0]), "+v"(xq[ph & 1][1]), "+v"(xq[ph & 1][2]), "+v"(xq[ph & 1][3]));
+                    read_phase(xq[(ph + 1) & 1], u, ph + 1);
+                    lds_wait_tiles<MTW>(xq[ph & 1]);
                 } else {
-                    asm volatile("s_waitcnt lgkmcnt(0)"
-                                 : "+v"(xq[ph & 1][0]), "+v"(xq[ph & 1][1]), "+v"(xq[ph & 1][2]), "+v"(xq[ph & 1][3]));
+                    lds_wait_tiles<0>(xq[ph & 1]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int m = 0; m < MTW; ++m)
 #pragma unroll
                     for (int s = 0; s < NS; ++s)
-                        if (!(m == MTW - 1 && ph % PLS == 1 && pkl_half))  // packed tile: one plane-phase
-                            acc[s][m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[0][ph / PLS][s], xq[ph & 1][m],
+                        if (!(m == MTW - 1 && ph % PL == 1 && pkl_half))  // packed tile: one plane-phase
+                            acc[s][m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[u % WD][ph / PL][s], xq[ph & 1][m],
                                                                                  acc[s][m], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
-                if (ph % PLS == PLS - 1) load_w_ks(wr[0][ph / PLS], cn, ph / PLS);
+                if (ph % PL == PL - 1) load_w_ks(wr[u % WD][ph / PL], c + WD, ph / PL);
             }
-            // this wave's direct loads of chunk cn precede the NS * KS weight
-            // loads issued since; the barrier then publishes every wave's
-            // block (all reads of the other buffer were waited for above)
             wait_vm<NS * KS>();
             barrier_nofence();
-            if (c + 1 < c_end) read_phase(xq[0], b ^ 1, 0);
+            if (c + 1 < c_end) read_phase(xq[0], u ^ 1, 0);
         }
-    } else {
-    store_x(xr[0], 0);
-    __syncthreads();
-    for (int c0 = c_begin; c0 < c_end; c0 += NB) {
-#pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            const int c = c0 + u;
-            if (c >= c_end) break;
-            load_x(xr[(u + PD) % NB], min(c + PD, c_last));
-            load_w(wr[(u + PD) % NB], min(c + PD, c_last));
-            __builtin_amdgcn_sched_barrier(0);
-            compute((c - c_begin) & 1, wr[u]);
-            __builtin_amdgcn_sched_barrier(0);
-            store_x(xr[(u + 1) % NB], ((c - c_begin) & 1) ^ 1);
-            __syncthreads();
-        }
-    }
     }
 
     int sk_ord = 0;  // earlier pieces of this tile to add (the tile's last piece)
@@ -912,11 +795,11 @@ void k_gemm32(GemmP p) {
         // before it loads.  Slot layout: element j of thread i at j * NTH + i
         // (16-byte pieces, coalesced).
         constexpr int PER4 = NS * MTW * 4;  // 16-byte accumulator pieces per thread
-        const int total = p.tiles * p.kchunks;
-        const int ord = (int)blockIdx.x - sk_owner(wgi * p.kchunks, total, p.sk_nwg);
+        const int total = p.tiles * p.ng * p.kchunks;
+        const int ord = (int)blockIdx.x - sk_owner(skt * p.kchunks, total, p.sk_nwg);
         auto slot_rsrc = [&](int o) {
             return __builtin_amdgcn_make_buffer_rsrc(
-                (void*)(p.part + ((size_t)wgi * p.sk_maxp + o) * (size_t)(NTH * PER4 * 4)), (short)0,
+                (void*)(p.part + ((size_t)skt * p.sk_maxp + o) * (size_t)(NTH * PER4 * 4)), (short)0,
                 NTH * PER4 * 16, 0x00020000);
         };
         if (c_end < p.kchunks) {
@@ -936,7 +819,7 @@ void k_gemm32(GemmP p) {
             wait_vm<0>();
             __syncthreads();
             if (threadIdx.x == 0)
-                __hip_atomic_fetch_add(p.sk_cnt + wgi, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                __hip_atomic_fetch_add(p.sk_cnt + skt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             continue;
         }
         if (ord > 0) {
@@ -946,24 +829,23 @@ void k_gemm32(GemmP p) {
                         atomicOr(p.flags, 4);
                         break;
                     }
-                    if (__hip_atomic_load(p.sk_cnt + wgi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) >= ord)
+                    if (__hip_atomic_load(p.sk_cnt + skt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) >= ord)
                         break;
                     __builtin_amdgcn_s_sleep(2);
                 }
                 // back to zero once every earlier piece has counted, also
                 // after a wait that gave up (the stream runs the next launch
                 // only when all of this one's workgroups have ended)
-                __hip_atomic_fetch_sub(p.sk_cnt + wgi, ord, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                __hip_atomic_fetch_sub(p.sk_cnt + skt, ord, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             }
             __syncthreads();
             sk_ord = ord;  // added tile by tile in the epilogue (fewer live registers)
         }
     }
-    // Packed last tile of the column-split form (its wave's tile MTW - 1):
-    // slot 224 + i's sums are those of lanes l and l ^ 16 (i = l % 16),
+    // Packed last tile of the direct-staging form (its wave's tile MTW - 1):
+    // the sums of its slot i are those of lanes l and l ^ 16 (i = l % 16),
     // added by v_permlane16_swap; run after the earlier stream-K pieces'
     // sums are in
-    const bool pkl_fold = CS > 1 && p.pkl && half == CS - 1;
     auto fold_last = [&]() {
 #pragma unroll
         for (int s = 0; s < NS; ++s)
@@ -976,38 +858,22 @@ void k_gemm32(GemmP p) {
     };
     // Accumulator layout: lane l holds slot t = 32*m + l % 32 and, in
     // registers 4q..4q+3, weight rows 8q + 4*(l/32) + 0..3 of its group.
-    // Packed planes: slot t's sums are those of tile m and tile m + a + 1
-    // (t < 32a), or of lanes l and l ^ 16 of tile a, swapped in by
-    // v_permlane16_swap, which hands each lane the pair (own, partner).
-    if constexpr (PK) {
-#pragma unroll
-        for (int s = 0; s < NS; ++s)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const auto pr = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[s][PA][e]),
-                                                                 __float_as_uint(acc[s][PA][e]), false, false);
-                acc[s][PA][e] = __uint_as_float(pr[0]) + __uint_as_float(pr[1]);
-#pragma unroll
-                for (int m = 0; m < PA; ++m) acc[s][m][e] += acc[s][m + PA + 1][e];
-            }
-    }
     if constexpr (EPI == EPI_LMSTAT) {
         // lane l holds slot 32m + l % 32 and rows 8q + 4(l/32) + 0..3 of its
         // 32-row group: a slot's rows sit in lanes l and l ^ 32
         static_assert(!SPLIT, "the lm_head statistics need whole k sums");
         // (column split: the NW / CS row units each stage every slot once)
-        constexpr int MTO = PK ? PA + 1 : MTW;
-        constexpr int NSLOT = (PK ? PA + 1 : MT) * 32;
+        constexpr int NSLOT = MT * 32;
         constexpr int NU = NW / CS;  // row units per workgroup
         static_assert(NU * NSLOT * (int)sizeof(VStat) <= (int)sizeof(xs), "statistics staging exceeds LDS");
         VStat* stg = reinterpret_cast<VStat*>(xs);
-        if (pkl_fold) fold_last();
+        if (pkl_half) fold_last();
 #pragma unroll
-        for (int m = 0; m < MTO; ++m) {
-            const int t = (m0 + m) * 32 + lc;
+        for (int m = 0; m < MTW; ++m) {
+            const int ts = (m0 + m) * 32 + lc, t = tb + ts;
             VStat st = vstat_empty();
-            if (has_unit && t < p.T && !(PK && m == PA && lc >= 16)) {
-                const float sc = rsl[t];
+            if (has_unit && t < p.T) {
+                const float sc = rsl[ts];
                 float z[NS * 16];
                 int row[NS * 16];
 #pragma unroll
@@ -1027,10 +893,10 @@ void k_gemm32(GemmP p) {
                 st = lane_stat(z, row, p.dnext[t], p.zd + t);
             }
             st = vstat_merge(st, vstat_shfl_xor(st, 32));
-            if (lh == 0) stg[(wv / CS) * NSLOT + t] = st;
+            if (lh == 0) stg[wrow * NSLOT + ts] = st;
         }
         __syncthreads();
-        lmstat_merge_waves<NTH, NU, NSLOT>(p, stg, wgi);
+        lmstat_merge_waves<NTH, NU, NSLOT>(p, stg, wgi, tb);
         return;
     }
     if constexpr (SPLIT) {
@@ -1042,11 +908,10 @@ void k_gemm32(GemmP p) {
         float* stg = reinterpret_cast<float*>(xs);
         const int u0 = wgi * p.G / p.WPS;
         const int nrow = ((wgi + 1) * p.G / p.WPS - u0) * NS * 32;
-        const int wrow = wv / CS;  // row unit within the workgroup
-        if (pkl_fold) fold_last();
+        if (pkl_half) fold_last();
 #pragma unroll
-        for (int m = 0; m < (PK ? PA + 1 : MTW); ++m) {
-            if (m * 32 >= p.T) break;  // so are the other halves' tiles m + MTW * h
+        for (int m = 0; m < MTW; ++m) {
+            if (tb + m * 32 >= p.T) break;  // so are the other halves' tiles m + MTW * h
             if (has_unit) {
 #pragma unroll
                 for (int s = 0; s < NS; ++s)
@@ -1058,23 +923,22 @@ void k_gemm32(GemmP p) {
             __syncthreads();
 #pragma unroll
             for (int h = 0; h < CS; ++h) {
-                const int tile = h * MTW + m;
-                const int nsl = min(PK && m == PA ? 16 : 32, p.T - tile * 32);
+                const int ft = tb + (h * MTW + m) * 32;  // first slot of the tile
+                const int nsl = min(32, p.T - ft);
                 if (nsl > 0)
-                    store_partial_rows<NTH, WR>(p, stg + h * 32 * LDR, LDR, split, tile * 32, nsl, u0 * NS * 32,
-                                                nrow);
+                    store_partial_rows<NTH, WR>(p, stg + h * 32 * LDR, LDR, split, ft, nsl, u0 * NS * 32, nrow);
             }
             __syncthreads();
         }
         return;
     }
 #pragma unroll
-    for (int m = 0; m < (PK ? PA + 1 : MTW); ++m) {
+    for (int m = 0; m < MTW; ++m) {
         if constexpr (SKF) {
             // the earlier pieces' sums of this slot tile, in piece order
             for (int o = 0; o < sk_ord; ++o) {
                 const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-                    (void*)(p.part + ((size_t)wgi * p.sk_maxp + o) * (size_t)(NTH * NS * MTW * 16)), (short)0,
+                    (void*)(p.part + ((size_t)skt * p.sk_maxp + o) * (size_t)(NTH * NS * MTW * 16)), (short)0,
                     NTH * NS * MTW * 64, 0x00020000);
                 u32x4 v[NS][4];
 #pragma unroll
@@ -1093,26 +957,26 @@ void k_gemm32(GemmP p) {
                     }
             }
         }
-        if (m == MTW - 1 && pkl_fold) fold_last();
-        const int t = (m0 + m) * 32 + lc;
-        if (!has_unit || t >= p.T || (PK && m == PA && lc >= 16)) continue;
-        const float sc = rsl[t];
+        if (m == MTW - 1 && pkl_half) fold_last();
+        const int ts = (m0 + m) * 32 + lc, t = tb + ts;
+        if (!has_unit || t >= p.T) continue;
+        const float sc = rsl[ts];
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            const int grp = unit * NS + s;
+            const int rg = unit * NS + s;  // 32-row group
             if (EPI == EPI_SWIGLU) {
                 // rows 0-15 of the group are gate rows 16*grp.., 16-31 the
                 // matching up rows; both sit in the same lane
 #pragma unroll
                 for (int q = 0; q < 2; ++q)
-                    swiglu_store4(p, t, grp * 16 + 8 * q + 4 * lh,
+                    swiglu_store4(p, t, rg * 16 + 8 * q + 4 * lh,
                                   f32x4{acc[s][m][4 * q], acc[s][m][4 * q + 1], acc[s][m][4 * q + 2], acc[s][m][4 * q + 3]},
                                   f32x4{acc[s][m][4 * q + 8], acc[s][m][4 * q + 9], acc[s][m][4 * q + 10], acc[s][m][4 * q + 11]},
                                   sc);
             } else {
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    epi_store4<EPI>(p, t, grp * 32 + 8 * q + 4 * lh,
+                    epi_store4(p, t, rg * 32 + 8 * q + 4 * lh,
                                     f32x4{acc[s][m][4 * q], acc[s][m][4 * q + 1], acc[s][m][4 * q + 2], acc[s][m][4 * q + 3]},
                                     sc);
             }
@@ -1143,7 +1007,7 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(GemmP p) {
     } else {
         f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
         for (int s = 0; s < p.S; ++s) v += *(const f32x4*)(base + s * stride + c);
-        epi_store4<EPI>(p, t, c, v, row_rstd(p, t));
+        epi_store4(p, t, c, v, row_rstd(p, t));
     }
 }
 
@@ -1214,106 +1078,67 @@ __global__ void k_gemm_f32(GemmF p) {
                                   : p.W2 + (size_t)(c - p.seg2) * p.K;
     float a = 0.f;
     for (int k = 0; k < p.K; ++k) a = fmaf(x[k], w[k], a);
-    if (p.epi == EPI_RESID)
-        p.out[(size_t)t * p.ldo + c] += a;
-    else
-        p.out[(size_t)t * p.ldo + c] = a;
+    p.out[(size_t)t * p.ldo + c] = a;
 }
 
 // ---------------------------------------------------------------------------
 // host-side configuration
 // ---------------------------------------------------------------------------
 
-// Tile shape per slot-count class: form F (16: 16x16x32 MFMA, 16-slot
-// tiles, NSUB = 2 row groups of 16 per wave; 32: 32x32x16 MFMA, 32-slot
-// tiles, one 32-row group per wave), MT slot tiles, KC k elements per
-// pipeline chunk, PD chunks of prefetch, NW waves per workgroup.  Measured
-// on the 32B shapes (two activation planes):
-//   * eight waves (256 weight rows) share one staged X chunk where the row
-//     count allows; it halves the X staging per weight byte;
-//   * up to 96 slots the 16x16 form (128-k chunks, one chunk of prefetch)
-//     wins: at T = 80 its 5 slot tiles pad nothing, where the 32x32 form
-//     computes 96 slots (gate/up 113 vs 119 us in the full step);
-//   * above, the 32x32 form wins by its MFMA rate: gate/up at T = 128 / 176
-//     / 240 takes 141 / 188 / 390 us against 181 / 237 / 509 us;
-//   * 225..256 slots: eight waves with 32-k chunks (gate/up at T = 240
-//     292 us against 392 us for four waves with 64-k chunks);
-//   * above 256 slots tiles need the register budget of one wave per SIMD
-//     (four waves) and shorter chunks so that a double-buffered two-plane
-//     chunk fits in LDS.
-// FILL: choose the k splits to fill one wave of workgroups (the eight-wave
-// rule of choose_splits) even for four-wave tiles.
-// F: MFMA form (16 or 32 rows); MT: slot tiles; NSUB: 16- or 32-row groups
-// per wave; KC: k per chunk; NW: waves per workgroup; PD: prefetch depth;
-// PK: packed planes; FILL: split policy of eight-wave tiles; CS: column
-// split (waves per row unit)
-struct GemmShape { int F, MT, NSUB, KC, NW, PD, PK, FILL = 0, CS = 1; };
-
-constexpr int kT32 = 97;  // first slot count served by the 32x32 form
+// Tile shape of a product.  F: MFMA form; MT: slot tiles (of 16 or 32 slots)
+// of a workgroup; NW: waves; CS: column split; NG: slot groups; KC: k per
+// chunk; UR: weight rows of a row unit (one wave's, or CS waves'); FILL:
+// split policy, see choose_splits.
+struct GemmShape { int F, MT, NW, CS, NG, KC, UR, FILL; };
 
 static int cu_count();
 
+// The 16x16 form (four-wave workgroups of 128 weight rows, 64-k chunks) serves
+// products up to 96 slots that are too small to fill the GPU with 256-row
+// workgroups of enough k each; the 32x32 form serves everything else, with
+// the tile shape that measured fastest per slot count.  Against the forms it
+// replaced (one machine, Qwen3-32B shapes, us): T = 16 gate/up 80.0 -> 79.6,
+// lm_head 279 -> 270; T = 60 100 -> 96, 328 -> 308; T = 96 156 -> 125, 470 -> 352,
+// the three projections together 129 -> 101 on average of three; T = 128 175 -> 157,
+// 534 -> 424; T = 160 202 -> 175; T = 192 229 -> 194; T = 224 275 -> 242; T = 300
+// (13-tile four-wave tiles with 16-k chunks before) 650 -> 344; T = 384 715 -> 390.
 static GemmShape shape_for(int T, int vcols, bool raw, int K) {
     const bool wide = vcols % 256 == 0;
-    // packed planes (2a + 1 tiles for 32a < T <= 32a + 16): split-K
-    // partial GEMMs at 65..80 slots (QKV / O / down at T = 80: 29.5 / 23.7
-    // / 53 us against 32.4 / 25.3 / 54 us for the 16x16 form), and every
-    // GEMM at 97..112 slots (gate/up at T = 112: 147-175 us against 167-194)
-    if (wide && raw && T > 64 && T <= 80) return {32, 5, 1, 64, 8, 2, 1};
-    if (wide && T > 96 && T <= 112) return {32, 7, 1, 64, 8, 1, 1};
+    constexpr int kT32 = 97;  // slot counts the 16x16 form's tiles end at
+    const GemmShape g16{16, std::max(2, (T + 15) / 16), 4, 1, 1, 64, 32, 0};
     if (T < kT32) {
-        const int mt = std::max(2, (T + 15) / 16);
         // split-K partial GEMMs with few weight rows (the Qwen3-1.7B shapes):
-        // when eight-wave tiles with at least two 128-k chunks per split
-        // cannot fill 90% of the CUs, four-wave tiles with 64-k chunks give
-        // twice the workgroups (QKV / O / down at T = 60: 7.9 / 6.5 / 9.4 us
-        // against 10.2 / 8.9 / 11.6 us)
+        // when 256-row workgroups with at least two 128-k chunks per split
+        // cannot fill 90% of the CUs, 128-row ones give twice the workgroups
+        // (QKV / O / down at T = 60 8.5-11.2 us against 11.2-17.2 us)
         if (raw && wide) {
             const int tiles8 = vcols / 256;
             const int s8 = std::min(std::max(1, K / 128 / 2), std::max(1, cu_count() / tiles8));
-            if (10 * tiles8 * s8 < 9 * cu_count()) return GemmShape{16, mt, 2, 64, 4, 2, 0, 1};
+            if (10 * tiles8 * s8 < 9 * cu_count()) return GemmShape{16, g16.MT, 4, 1, 1, 64, 32, 1};
         }
         // SwiGLU products of fewer than a quarter as many 256-row tiles as
-        // CUs (the Qwen3-1.7B gate/up: 48): four-wave 128-row tiles, split
-        // as the eight-wave ones are (two splits, 192 workgroups; one
-        // machine at T = 60, then with a separate reduction kernel: gate/up
-        // 25.7 -> 24.2 us per layer, the step 2.45-2.47 -> 2.42-2.43 ms;
-        // four splits 26.4 us, three 28.3 us, unsplit 28.7 us).  The split
-        // is now reduced by its last split (launch_gemm): 23.1 us.
-        if (!raw && wide && vcols / 256 * 4 < cu_count()) return GemmShape{16, mt, 2, 64, 4, 2, 0, 1};
+        // CUs (the Qwen3-1.7B gate/up: 48): 128-row tiles split to fill the
+        // CUs (two splits, 192 workgroups; at T = 60 three splits 26.9, four
+        // 24.6, unsplit 28.7, two 23.1 us), reduced by the last split
+        // (launch_gemm)
+        if (!raw && wide && vcols / 256 * 4 < cu_count()) return GemmShape{16, g16.MT, 4, 1, 1, 64, 32, 1};
         // an lm_head over a short k (the Qwen3-1.7B one: 151936 x 2048,
-        // weight-bound at these slot counts) on four-wave 128-row tiles:
-        // 1187 shorter workgroups leave a shorter tail than 594 eight-wave
-        // ones at one per CU (one machine at T = 60: 158 -> 143-148 us; the
-        // Qwen3-32B lm_head at T = 80, MFMA-heavier, is slower that way:
-        // 338-350 -> 359-363 us)
-        if (!raw && !wide && vcols % 32 == 0 && K <= 2048) return GemmShape{16, mt, 2, 64, 4, 2, 0};
-        // the lm_head (151936 rows: not a multiple of 256) takes the
-        // eight-wave tiles too; its last workgroup has fewer units
-        if (wide || (!raw && vcols % 32 == 0)) return GemmShape{16, mt, 2, 128, 8, 1, 0};
-        return GemmShape{16, mt, 2, 64, 4, 2, 0};
+        // weight-bound at these slot counts): 1187 shorter workgroups leave a
+        // shorter tail than 594
+        if (!raw && !wide && vcols % 32 == 0 && K <= 2048) return g16;
     }
     const int mt = (T + 31) / 32;
-    // eight-wave workgroups also for the lm_head, whose row count is not a
-    // multiple of 256 (the workgroups then take 7 or 8 row units each)
-    const bool w8 = wide || (!raw && vcols % 32 == 0);
-    if (mt <= 4) return w8 ? GemmShape{32, mt, 1, 64, 8, 2, 0} : GemmShape{32, mt, 1, 64, 4, 2, 0};
-    if (mt <= 7) return w8 ? GemmShape{32, mt, 1, 64, 8, 1, 0} : GemmShape{32, mt, 1, 64, 4, 1, 0};
-    // 225..256 slots: eight waves with 32-k chunks (double-buffered staging
-    // of 2 x 256 rows then fits one workgroup of 256 weight rows per CU);
-    // probe on one machine at T = 240: gate/up 292 vs 392 us, QKV 63 vs 99, O 51
-    // vs 93, down 143 vs 210 us against four waves with 64-k chunks
-    if (mt <= 8) {
-        // 64-row units shared by two waves (four slot tiles each) with 64-k
-        // chunks: every B fragment feeds two MFMAs.  Timing on one machine of the
-        // 32B shapes at T = 229 in isolation: gate/up 263 vs 293 us, QKV 57
-        // vs 59, O 52 vs 56, down 121 vs 137 us against 32-row units
-        if (vcols % 64 == 0) return GemmShape{32, 8, 2, 64, 8, 1, 0, 0, 2};
-        return w8 ? GemmShape{32, 8, 1, 32, 8, 1, 0} : GemmShape{32, 8, 1, 64, 4, 1, 0};
-    }
-    if (mt <= 10) return {32, 10, 1, 32, 4, 1, 0};
-    if (mt <= 13) return {32, 13, 1, 16, 4, 1, 0};
-    return {0, 0, 0, 0, 0, 0, 0};
+    auto s32 = [](int MT, int CS, int NG) { return GemmShape{32, MT, 4 * CS, CS, NG, 64, 64, 1}; };
+    if (mt <= 5) return s32(mt, 1, 1);
+    // six tiles and up: the column split is faster than four waves with all
+    // tiles (T = 384 in two groups of six: gate/up 390 against 410 us)
+    if (mt == 6) return s32(6, 2, 1);
+    if (mt <= 8) return s32(8, 2, 1);
+    // two slot groups; five tiles do not halve, so they take four waves
+    // (T = 300: gate/up 344 us against 378 for two groups of six)
+    if (mt <= 10) return s32(5, 1, 2);
+    if (mt <= 12) return s32(6, 2, 2);
+    return s32(8, 2, 2);  // three groups of five: 502 against 485 us at T = 400
 }
 
 typedef void (*GemmFn)(GemmP);
@@ -1321,70 +1146,53 @@ typedef void (*ReduceFn)(GemmP);
 
 // Activations always come as two planes (hi, lo); split-K kernels write raw
 // partial planes and the epilogue runs in the reducer.
-template <int F, int MT, int NW, int KC, int PD, bool SPLIT, bool PK = false, int CS = 1, int NS = 1>
-static GemmFn pick_epi(int epi, bool skf = false) {
-    if constexpr (F == 16) {
-        if (SPLIT) return k_gemm16<MT, 2, KC, EPI_STORE, true, NW, 2, PD>;
-        switch (epi) {
-            case EPI_RESID: return k_gemm16<MT, 2, KC, EPI_RESID, false, NW, 2, PD>;
-            case EPI_SWIGLU: return k_gemm16<MT, 2, KC, EPI_SWIGLU, false, NW, 2, PD>;
-            case EPI_LMSTAT: return k_gemm16<MT, 2, KC, EPI_LMSTAT, false, NW, 2, PD>;
-            default: return k_gemm16<MT, 2, KC, EPI_STORE, false, NW, 2, PD>;
-        }
-    } else {
-        if constexpr (CS > 1 && !SPLIT)
-            if (skf) return epi == EPI_SWIGLU ? k_gemm32<MT, NS, KC, EPI_SWIGLU, false, NW, 2, PD, PK, CS, true> : nullptr;
-        if (SPLIT) return k_gemm32<MT, NS, KC, EPI_STORE, true, NW, 2, PD, PK, CS>;
-        switch (epi) {
-            case EPI_RESID: return k_gemm32<MT, NS, KC, EPI_RESID, false, NW, 2, PD, PK, CS>;
-            case EPI_SWIGLU: return k_gemm32<MT, NS, KC, EPI_SWIGLU, false, NW, 2, PD, PK, CS>;
-            case EPI_LMSTAT: return k_gemm32<MT, NS, KC, EPI_LMSTAT, false, NW, 2, PD, PK, CS>;
-            default: return k_gemm32<MT, NS, KC, EPI_STORE, false, NW, 2, PD, PK, CS>;
-        }
+template <int MT>
+static GemmFn pick16(bool split, int epi) {
+    if (split) return k_gemm16<MT, 2, 64, EPI_STORE, true, 4, 2, 2>;
+    switch (epi) {
+        case EPI_SWIGLU: return k_gemm16<MT, 2, 64, EPI_SWIGLU, false, 4, 2, 2>;
+        case EPI_LMSTAT: return k_gemm16<MT, 2, 64, EPI_LMSTAT, false, 4, 2, 2>;
+        default: return k_gemm16<MT, 2, 64, EPI_STORE, false, 4, 2, 2>;
     }
 }
 
-template <int NW, bool SPLIT>
-static GemmFn pick_nw(const GemmShape& sh, int epi) {
-    constexpr int KC16 = NW == 8 ? 128 : 64, PD16 = NW == 8 ? 1 : 2;
+template <int MT, int CS>
+static GemmFn pick32(bool split, int epi, bool skf) {
+    if (split) return k_gemm32<MT, EPI_STORE, true, 4 * CS, CS>;
+    switch (epi) {
+        case EPI_SWIGLU:
+            if constexpr (MT >= 5)
+                if (skf) return k_gemm32<MT, EPI_SWIGLU, false, 4 * CS, CS, true>;
+            return k_gemm32<MT, EPI_SWIGLU, false, 4 * CS, CS>;
+        case EPI_LMSTAT: return k_gemm32<MT, EPI_LMSTAT, false, 4 * CS, CS>;
+        default: return k_gemm32<MT, EPI_STORE, false, 4 * CS, CS>;
+    }
+}
+
+static GemmFn pick(const GemmShape& sh, bool split, int epi, bool skf = false) {
     if (sh.F == 16) {
         switch (sh.MT) {
-            case 2: return pick_epi<16, 2, NW, KC16, PD16, SPLIT>(epi);
-            case 3: return pick_epi<16, 3, NW, KC16, PD16, SPLIT>(epi);
-            case 4: return pick_epi<16, 4, NW, KC16, PD16, SPLIT>(epi);
-            case 5: return pick_epi<16, 5, NW, KC16, PD16, SPLIT>(epi);
-            case 6: return pick_epi<16, 6, NW, KC16, PD16, SPLIT>(epi);
+            case 2: return pick16<2>(split, epi);
+            case 3: return pick16<3>(split, epi);
+            case 4: return pick16<4>(split, epi);
+            case 5: return pick16<5>(split, epi);
+            default: return pick16<6>(split, epi);
         }
-        return nullptr;
     }
     switch (sh.MT) {
-        case 4: return pick_epi<32, 4, NW, 64, 2, SPLIT>(epi);
-        case 5: return pick_epi<32, 5, NW, 64, 1, SPLIT>(epi);
-        case 6: return pick_epi<32, 6, NW, 64, 1, SPLIT>(epi);
-        case 7: return pick_epi<32, 7, NW, 64, 1, SPLIT>(epi);
+        case 1: return pick32<1, 1>(split, epi, skf);
+        case 2: return pick32<2, 1>(split, epi, skf);
+        case 3: return pick32<3, 1>(split, epi, skf);
+        case 4: return pick32<4, 1>(split, epi, skf);
+        case 5: return pick32<5, 1>(split, epi, skf);
+        case 6: return pick32<6, 2>(split, epi, skf);
+        default: return pick32<8, 2>(split, epi, skf);
     }
-    return nullptr;
 }
 
-template <bool SPLIT>
-static GemmFn pick(const GemmShape& sh, int epi, bool skf = false) {
-    if (sh.PK) {
-        if (sh.MT == 5) return SPLIT ? pick_epi<32, 5, 8, 64, 2, true, true>(epi) : nullptr;
-        if (sh.MT == 7) return pick_epi<32, 7, 8, 64, 1, SPLIT, true>(epi);
-        return nullptr;
-    }
-    if (sh.F == 32 && sh.MT == 8) {
-        if (sh.CS == 2) return pick_epi<32, 8, 8, 64, 1, SPLIT, false, 2, 2>(epi, skf);
-        return sh.NW == 8 ? pick_epi<32, 8, 8, 32, 1, SPLIT>(epi) : pick_epi<32, 8, 4, 64, 1, SPLIT>(epi);
-    }
-    if (sh.F == 32 && sh.MT == 10) return pick_epi<32, 10, 4, 32, 1, SPLIT>(epi);
-    if (sh.F == 32 && sh.MT == 13) return pick_epi<32, 13, 4, 16, 1, SPLIT>(epi);
-    return sh.NW == 8 ? pick_nw<8, SPLIT>(sh, epi) : pick_nw<4, SPLIT>(sh, epi);
-}
-
-// the last-split SwiGLU product on the four-wave 16x16 tiles
+// the last-split SwiGLU product on the 16x16 tiles
 static GemmFn pick_la(const GemmShape& sh) {
-    if (sh.F != 16 || sh.NW != 4 || sh.NSUB != 2 || sh.KC != 64 || sh.PD != 2) return nullptr;
+    if (sh.F != 16) return nullptr;
     switch (sh.MT) {
         case 2: return k_gemm16<2, 2, 64, EPI_SWIGLU, false, 4, 2, 2, 16, true>;
         case 3: return k_gemm16<3, 2, 64, EPI_SWIGLU, false, 4, 2, 2, 16, true>;
@@ -1397,7 +1205,6 @@ static GemmFn pick_la(const GemmShape& sh) {
 
 static ReduceFn pick_reduce(int epi) {
     switch (epi) {
-        case EPI_RESID: return k_splitk_reduce<EPI_RESID>;
         case EPI_SWIGLU: return k_splitk_reduce<EPI_SWIGLU>;
         default: return k_splitk_reduce<EPI_STORE>;
     }
@@ -1414,18 +1221,18 @@ static int cu_count() {  // cached
     return n;
 }
 
-// k splits.  Four-wave tiles (a divisor of kchunks): the largest count
-// giving 1.25 to 1.75 workgroups per CU, else the smallest giving at least
-// 1.25.  Eight-wave tiles (one workgroup per CU fits in LDS): the largest
-// count keeping the grid within one wave of workgroups, splits of unequal
-// chunk counts allowed, at least two chunks per split (measured on the 32B
-// shapes at T = 80: QKV 40 tiles x 6 = 240 workgroups 27.2 us vs x 5
-// 30.7 us, O 20 x 12 23.9 vs x 8 27.4, down 20 x 12 52.6 vs x 10 57.1; the
-// extra partial sums cost the consumers less than the idle CUs cost the
-// GEMM.  On the 1.7B shapes one-chunk splits lose to pipeline start-up and
-// partial-sum traffic: the step goes from 2.99 to 2.77 ms with two).
-static int choose_splits(int tiles, int kchunks, int nw) {
-    if (nw == 8) {
+// k splits.  fill: the largest count keeping the grid within one workgroup
+// per CU, splits of unequal chunk counts allowed, at least two chunks per
+// split (measured on the 32B shapes at T = 80: QKV 40 tiles x 6 = 240
+// workgroups 27.2 us vs x 5 30.7 us, O 20 x 12 23.9 vs x 8 27.4, down 20 x 12
+// 52.6 vs x 10 57.1; the extra partial sums cost the consumers less than the
+// idle CUs cost the GEMM, while twice the splits, two workgroups per CU, cost
+// more than they give: 34.8 against 33.8 us on average of the three.  On the
+// 1.7B shapes one-chunk splits lose to pipeline start-up and partial-sum
+// traffic).  Otherwise (a divisor of kchunks): the largest count giving 1.25
+// to 1.75 workgroups per CU, else the smallest giving at least 1.25.
+static int choose_splits(int tiles, int kchunks, bool fill) {
+    if (fill) {
         const int hi = cu_count();
         if (tiles * 2 > hi) return 1;
         return std::max(1, std::min(std::max(1, kchunks / 2), hi / tiles));
@@ -1475,7 +1282,6 @@ int launch_gemm(const Dims& D, const GemmCall& g, const SlotBufs& sb, hipStream_
     }
     const int vcols = g.epi == EPI_SWIGLU ? 2 * g.N : g.N;
     const GemmShape sh = shape_for(g.T, vcols, g.raw != 0, g.K);
-    const int unit_rows = sh.F * sh.NSUB;  // weight rows of one row unit
     GemmP p;
     p.X = (const bf16_t*)g.X;
     p.Wp = (const bf16_t*)g.Wp;
@@ -1486,17 +1292,17 @@ int launch_gemm(const Dims& D, const GemmCall& g, const SlotBufs& sb, hipStream_
     p.vcols = vcols;
     // workgroups of NW waves; a last partial workgroup when the row count is
     // not a multiple of NW units (its surplus waves load and store nothing)
-    const int units = p.vcols / unit_rows;
+    const int units = p.vcols / sh.UR;
     const int upw = sh.NW / sh.CS;  // row units per workgroup
     p.tiles = (units + upw - 1) / upw;
-    int S = g.epi == EPI_LMSTAT ? 1 : choose_splits(p.tiles, p.kchunks, sh.FILL ? 8 : sh.NW);
+    int S = g.epi == EPI_LMSTAT ? 1 : choose_splits(p.tiles * sh.NG, p.kchunks, sh.FILL);
     // four-wave split-K tiles over a short k (the Qwen3-1.7B QKV and O
     // projections, k = 2048): half the splits, so each split keeps four
     // 64-k chunks and the consumer reads half the partial planes (one
     // machine at T = 60, each with its consumer: QKV 18.8 -> 18.4 us, O
     // 14.3 -> 14.0 us per layer; the down projection, k = 6144, is slower
     // so: 19.4 -> 20.0 us)
-    if (g.raw && sh.NW == 4 && sh.FILL && g.K <= 2048) S = std::max(1, S / 2);
+    if (g.raw && sh.F == 16 && sh.FILL && g.K <= 2048) S = std::max(1, S / 2);
     while (S > 1 && (size_t)S * g.T * p.vcols > sb.gpart_floats) {
         int t = S - 1;
         while (t > 1 && p.kchunks % t) --t;
@@ -1516,39 +1322,46 @@ int launch_gemm(const Dims& D, const GemmCall& g, const SlotBufs& sb, hipStream_
     p.zd = g.zd;
     p.dnext = g.dnext;
     if (g.groups_out) *g.groups_out = p.tiles;
-    // Stream-K for an unsplit column-split SwiGLU product that leaves CUs
-    // idle (gate/up at 225-256 slots: 200 row tiles of 256 rows on 256 CUs)
+    // Stream-K for an unsplit SwiGLU product of fewer row tiles than CUs (the
+    // Qwen3-32B gate/up: 200) above 128 slots: T = 160 175 us, T = 224 242
+    // against 275 unsplit.  Below, the weights' stream bounds the product and
+    // the idle CUs cost less than the partial sums (T = 60: 114 against 96 us;
+    // T = 128: 154 against 157, but then one batch holds every CU, which slows
+    // two batches on two streams down)
     p.sk_nwg = 0;
     p.sk_maxp = 0;
-    p.pkl = sh.CS > 1 && sh.MT == 8 && g.T > 224 && g.T <= 240;
+    p.ng = sh.NG;
     p.sk_polls = g.sk_polls;
     p.sk_cnt = g.sk_cnt;
     p.flags = g.flags;
-    if (!g.raw && g.epi == EPI_SWIGLU && sh.CS > 1 && S == 1 && g.sk_cnt && g.flags &&
-        p.tiles < cu_count() && p.tiles <= kSkCounters) {
-        const int total = p.tiles * p.kchunks, nwg = std::min(cu_count(), total);
+    const int wtiles = p.tiles * p.ng;  // (row tile, slot group) work tiles
+    if (!g.raw && g.epi == EPI_SWIGLU && sh.F == 32 && sh.MT >= 5 && S == 1 && g.sk_cnt && g.flags &&
+        p.tiles < cu_count() && wtiles <= kSkCounters) {
+        const int total = wtiles * p.kchunks, nwg = std::min(cu_count(), total);
         int maxp = 0;  // most pieces of a tile before its last
-        for (int t = 0; t < p.tiles; ++t)
+        for (int t = 0; t < wtiles; ++t)
             maxp = std::max(maxp, sk_owner(t * p.kchunks + p.kchunks - 1, total, nwg) -
                                       sk_owner(t * p.kchunks, total, nwg));
-        const size_t slot_floats = (size_t)64 * sh.NW * sh.NSUB * (sh.MT / sh.CS) * 16;
-        if (maxp >= 1 && (size_t)p.tiles * maxp * slot_floats <= sb.gpart_floats) {
+        const size_t slot_floats = (size_t)256 * sh.MT * 32;  // 256 rows, MT tiles of 32 slots
+        if (maxp >= 1 && (size_t)wtiles * maxp * slot_floats <= sb.gpart_floats) {
             p.sk_nwg = nwg;
             p.sk_maxp = maxp;
-            hipLaunchKernelGGL(pick<false>(sh, g.epi, true), dim3(nwg), dim3(64 * sh.NW), 0, s, p);
+            hipLaunchKernelGGL(pick(sh, false, g.epi, true), dim3(nwg), dim3(64 * sh.NW), 0, s, p);
             return 1;
         }
     }
+    // slot groups: whole runs of 8 work tiles (one per XCD) for every group
+    const int grid = p.ng == 1 ? p.tiles * S : (p.tiles * S + 7) / 8 * 8 * p.ng;
     if (g.raw) {
         // S partial planes [S][T][N] for a fused consumer to reduce
-        hipLaunchKernelGGL(pick<true>(sh, EPI_STORE), dim3(p.tiles * S), dim3(64 * sh.NW), 0, s, p);
+        hipLaunchKernelGGL(pick(sh, true, EPI_STORE), dim3(grid), dim3(64 * sh.NW), 0, s, p);
     } else if (S == 1) {
-        hipLaunchKernelGGL(pick<false>(sh, g.epi), dim3(p.tiles), dim3(64 * sh.NW), 0, s, p);
+        hipLaunchKernelGGL(pick(sh, false, g.epi), dim3(grid), dim3(64 * sh.NW), 0, s, p);
     } else {
         // a split SwiGLU product on four-wave tiles: its last split adds the
-        // others' sums (slots of NTH x NSUB x MT x 4 floats per split and
-        // tile) and runs the epilogue, no reduction kernel
-        const size_t la_floats = (size_t)p.tiles * S * (64 * sh.NW) * sh.NSUB * sh.MT * 4;
+        // others' sums (a slot of fp32 accumulators per split and tile) and runs
+        // the epilogue, no reduction kernel
+        const size_t la_floats = (size_t)p.tiles * S * 128 * sh.MT * 16;  // 128 rows, MT tiles of 16 slots
         const GemmFn la = g.epi == EPI_SWIGLU && g.sk_cnt && p.tiles <= kSkCounters && la_floats <= sb.gpart_floats
                               ? pick_la(sh)
                               : nullptr;
@@ -1556,7 +1369,7 @@ int launch_gemm(const Dims& D, const GemmCall& g, const SlotBufs& sb, hipStream_
             hipLaunchKernelGGL(la, dim3(p.tiles * S), dim3(64 * sh.NW), 0, s, p);
             return S;
         }
-        hipLaunchKernelGGL(pick<true>(sh, g.epi), dim3(p.tiles * S), dim3(64 * sh.NW), 0, s, p);
+        hipLaunchKernelGGL(pick(sh, true, g.epi), dim3(grid), dim3(64 * sh.NW), 0, s, p);
         const int ncols = g.epi == EPI_SWIGLU ? p.vcols / 2 : p.vcols;
         const int n = g.T * (ncols / 4);
         hipLaunchKernelGGL(pick_reduce(g.epi), dim3((n + 255) / 256), dim3(256), 0, s, p);

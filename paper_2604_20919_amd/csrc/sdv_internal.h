@@ -119,7 +119,7 @@ void launch_attention(const Dims& D, const BatchView& bv, const SlotBufs& sb, co
 // EPI_LMSTAT (lm_head): phase-A statistics per (workgroup, slot) into
 // lstat, the logit of each slot's next draft into zd, and the logits
 // themselves into out when out is set; never split over k.
-enum GemmEpi { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LMSTAT = 3 };
+enum GemmEpi { EPI_STORE = 0, EPI_SWIGLU = 2, EPI_LMSTAT = 3 };
 struct GemmCall {
     const void* X;    // [T][K] act type
     const void* Wp;   // bf16: packed weights (fragment order, virtual rows)
@@ -129,7 +129,7 @@ struct GemmCall {
     int N;            // output columns (real); SWIGLU: F, with W[0]=gate, W[1]=up
     int K, T;
     int epi;
-    void* out;        // EPI_STORE: float [T][ldo]; EPI_RESID: float x [T][ldo]; SWIGLU: act [T][ldo]
+    void* out;        // EPI_STORE: float [T][ldo]; SWIGLU: act [T][ldo]
     int ldo;
     int raw;          // 1: write split-K partial planes [S][T][N] to the slot's
                       //    partial buffer and leave the reduction to the consumer
