@@ -546,9 +546,99 @@ __global__ void k_kv_copy(KVPool kv, KVCopyPages pages, int layer, int pos0, int
     }
 }
 
+// bf16 configuration (head_dim 128), caller rows 16-byte aligned: one wave
+// per (page, KV head).  The K block is the head's 16 rows one after another
+// (16-byte pieces both ways); the V block is their transpose, taken through
+// LDS so that both sides move 16 bytes a lane (the element-wise kernel above
+// touches the pool's V two bytes at a 32-byte stride).  Bound by HBM: 33.5 MB
+// for 4096 tokens of one Qwen3-32B-shaped layer.  Rows of the page outside
+// [pos0, pos0 + n) are neither read from nor written to either side.
+template <bool TO_POOL>
+__global__ __launch_bounds__(256) void k_kv_copy_page(KVPool kv, KVCopyPages pages, int layer, int pos0,
+                                                      int n, int npages, bf16_t* k, bf16_t* v) {
+    constexpr int HD = 128, ROW = HD + 8;  // padded staging row (elements)
+    __shared__ __attribute__((aligned(16))) bf16_t st[4][kPageTokens * ROW];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int item = blockIdx.x * 4 + wave;
+    const int hkv = kv.hkv;
+    const int pg = item / hkv, g = item % hkv;  // page of this launch, head
+    if (pg >= npages) return;
+    const int t0 = (pages.page0 + pg) * kPageTokens;        // position of the page's first token
+    const int lo = max(pos0 - t0, 0), hi = min(pos0 + n - t0, kPageTokens);  // its tokens of this copy
+    bf16_t* kp = (bf16_t*)kv.base + kv.k_off(layer, pages.id[pg], g);
+    bf16_t* vp = (bf16_t*)kv.base + kv.v_off(layer, pages.id[pg], g);
+    // row lane / 16 + 4 * i of the page, elements 8 * (lane % 16) ..
+    const int c = (lane & 15) * 8;
+    bf16_t* const sw = st[wave];
+    auto row = [&](bf16_t* base, int t) { return base + ((size_t)(t0 + t - pos0) * hkv + g) * HD + c; };
+    if (TO_POOL) {
+        uint4 kr[4], vr[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int t = (lane >> 4) + 4 * i;
+            const bool on = t >= lo && t < hi;
+            kr[i] = on ? *(const uint4*)row(k, t) : uint4{0, 0, 0, 0};
+            vr[i] = on ? *(const uint4*)row(v, t) : uint4{0, 0, 0, 0};
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int t = (lane >> 4) + 4 * i;
+            if (t >= lo && t < hi) *(uint4*)(kp + t * HD + c) = kr[i];
+            *(uint4*)(sw + t * ROW + c) = vr[i];
+        }
+        // (one wave: its LDS accesses are in order, the compiler waits for them)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int d = lane + 64 * i;
+            uint32_t w[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                w[q] = (uint32_t)sw[(2 * q) * ROW + d] | ((uint32_t)sw[(2 * q + 1) * ROW + d] << 16);
+            bf16_t* o = vp + d * kPageTokens;
+            if (lo == 0 && hi == kPageTokens) {
+                *(uint4*)o = uint4{w[0], w[1], w[2], w[3]};
+                *(uint4*)(o + 8) = uint4{w[4], w[5], w[6], w[7]};
+            } else {
+#pragma unroll
+                for (int t = 0; t < kPageTokens; ++t)
+                    if (t >= lo && t < hi) o[t] = (bf16_t)(w[t >> 1] >> (16 * (t & 1)));
+            }
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int d = lane + 64 * i;
+            const uint4 a = *(const uint4*)(vp + d * kPageTokens), b = *(const uint4*)(vp + d * kPageTokens + 8);
+            const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+            for (int t = 0; t < kPageTokens; ++t) sw[t * ROW + d] = (bf16_t)(w[t >> 1] >> (16 * (t & 1)));
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int t = (lane >> 4) + 4 * i;
+            if (t < lo || t >= hi) continue;
+            *(uint4*)row(k, t) = *(const uint4*)(kp + t * HD + c);
+            *(uint4*)row(v, t) = *(const uint4*)(sw + t * ROW + c);
+        }
+    }
+}
+
 void launch_kv_copy(const Dims& D, const KVPool& kv, const KVCopyPages& pages, int layer,
                     int pos0, int n, const void* k, const void* v, int to_pool, hipStream_t s) {
     if (n <= 0) return;
+    // whole 16-byte pieces need aligned caller rows (their stride is a
+    // multiple of 256 bytes); other pointers take the element-wise kernel
+    if (D.bf16 && (((uintptr_t)k | (uintptr_t)v) & 15) == 0) {
+        const int npages = (pos0 + n - 1) / kPageTokens - pages.page0 + 1;
+        const int blocks = (npages * D.hkv + 3) / 4;
+        if (to_pool)
+            hipLaunchKernelGGL(k_kv_copy_page<true>, dim3(blocks), dim3(256), 0, s, kv, pages, layer, pos0, n,
+                               npages, (bf16_t*)k, (bf16_t*)v);
+        else
+            hipLaunchKernelGGL(k_kv_copy_page<false>, dim3(blocks), dim3(256), 0, s, kv, pages, layer, pos0, n,
+                               npages, (bf16_t*)k, (bf16_t*)v);
+        return;
+    }
     if (D.bf16)
         hipLaunchKernelGGL(k_kv_copy<bf16_t>, dim3(n, D.hkv), dim3(128), 0, s, kv, pages,
                            layer, pos0, n, (bf16_t*)k, (bf16_t*)v, to_pool);
