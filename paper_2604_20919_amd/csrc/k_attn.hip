@@ -29,7 +29,7 @@
 // (row max, row sum, unnormalised output); a combine kernel merges the
 // partials of a row's chunks in chunk order, so results are deterministic.
 //
-// fp32 path: one wave per (slot, query head), plain loop over the context.
+// fp32 path: one workgroup per (slot, query head), lanes over tokens.
 #include "sdv_device.h"
 #include "sdv_internal.h"
 
@@ -451,48 +451,99 @@ __global__ __launch_bounds__(256) void k_attn_combine(BatchView bv, const float*
     st_act4(out, (size_t)bv.T * hq * HD, ((size_t)t * hq + h) * HD + 4 * l, o);
 }
 
-// fp32 path: one wave per (slot, query head); lanes split head_dim
+// fp32 path: one workgroup per (slot, query head); its four waves take every
+// fourth block of 64 tokens and are merged in wave order.  Scores: lane =
+// token (its key row in 16-byte pieces where rows are aligned); the softmax is
+// online per block, one pair of wave reductions per 64 tokens; outputs: lane =
+// dim, the 64 weights broadcast from LDS against the dim-major value blocks.
+// (One wave per row with a reduction per token took 98 us for 113 tokens of
+// four heads and 16 slots; this takes 7.4.)
+template <bool VEC>
 __global__ __launch_bounds__(256) void k_attn_f32(BatchView bv, const float* q, KVPool kv,
                                                   int layer, float* out, int hq, int hkv, int hd,
                                                   float scale) {
-    const int wave = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    const int t = wave / hq, h = wave % hq;
-    if (t >= bv.T) return;
+    __shared__ float qs[128];
+    __shared__ __attribute__((aligned(16))) float ps[4][64];
+    __shared__ float ms[4], ls[4], os[4][128];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int t = blockIdx.x / hq, h = blockIdx.x % hq;
     const int G = hq / hkv, g = h / G;
     const int b = bv.slot_b[t];
     const int n = bv.prefix[b] + bv.slot_j[t] + 1;
     const int32_t* pt = bv.page_table + (size_t)b * bv.max_pages;
     const float* base = (const float*)kv.base;
-    const float* qv = q + ((size_t)t * hq + h) * hd;
+    if (threadIdx.x < hd) qs[threadIdx.x] = q[((size_t)t * hq + h) * hd + threadIdx.x];
+    __syncthreads();
     float m = -INFINITY, l = 0.f, a0 = 0.f, a1 = 0.f;
-    const float q0 = lane < hd ? qv[lane] : 0.f, q1 = lane + 64 < hd ? qv[lane + 64] : 0.f;
-    for (int tok = 0; tok < n; ++tok) {
-        const int page = pt[tok >> 4], off = tok & 15;
-        const float* kr = base + kv.k_off(layer, page, g) + (size_t)off * hd;
-        const float* vb = base + kv.v_off(layer, page, g);
-        float d = (lane < hd ? q0 * kr[lane] : 0.f) + (lane + 64 < hd ? q1 * kr[lane + 64] : 0.f);
-        d = wave_sum(d) * scale;
-        const float mn = fmaxf(m, d);
+    for (int c0 = wave * 64; c0 < n; c0 += 256) {
+        const int tok = c0 + lane;
+        float d = -INFINITY;
+        if (tok < n) {
+            const float* kr = base + kv.k_off(layer, pt[tok >> 4], g) + (size_t)(tok & 15) * hd;
+            float s = 0.f;
+            if (VEC) {
+                for (int a = 0; a < hd; a += 4) {
+                    const f32x4 v = *(const f32x4*)(kr + a);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) s = fmaf(qs[a + e], v[e], s);
+                }
+            } else {
+                for (int a = 0; a < hd; ++a) s = fmaf(qs[a], kr[a], s);
+            }
+            d = s * scale;
+        }
+        const float mn = fmaxf(m, wave_max(d));
         const float al = expf(m - mn), pe = expf(d - mn);
-        l = l * al + pe;
-        if (lane < hd) a0 = a0 * al + pe * vb[(size_t)lane * kPageTokens + off];
-        if (lane + 64 < hd) a1 = a1 * al + pe * vb[(size_t)(lane + 64) * kPageTokens + off];
+        l = l * al + wave_sum(pe);
         m = mn;
+        a0 *= al;
+        a1 *= al;
+        ps[wave][lane] = pe;  // read back by the same wave
+        const int nt = min(64, n - c0);
+        for (int p0 = 0; p0 < nt; p0 += kPageTokens) {
+            const float* vb = base + kv.v_off(layer, pt[(c0 + p0) >> 4], g);
+#pragma unroll
+            for (int u = 0; u < kPageTokens; u += 4) {
+                const f32x4 pv = *(const f32x4*)&ps[wave][p0 + u];
+                const f32x4 z = f32x4{0.f, 0.f, 0.f, 0.f};
+                const f32x4 v0 = lane < hd ? *(const f32x4*)(vb + (size_t)lane * kPageTokens + u) : z;
+                const f32x4 v1 = lane + 64 < hd ? *(const f32x4*)(vb + (size_t)(lane + 64) * kPageTokens + u) : z;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (p0 + u + e >= nt) continue;  // rows past the context may hold anything
+                    a0 = fmaf(pv[e], v0[e], a0);
+                    a1 = fmaf(pv[e], v1[e], a1);
+                }
+            }
+        }
     }
-    float* dst = out + ((size_t)t * hq + h) * hd;
-    if (lane < hd) dst[lane] = a0 / l;
-    if (lane + 64 < hd) dst[lane + 64] = a1 / l;
+    if (lane == 0) {
+        ms[wave] = m;
+        ls[wave] = l;
+    }
+    os[wave][lane] = a0;
+    os[wave][lane + 64] = a1;
+    __syncthreads();
+    if ((int)threadIdx.x >= hd) return;
+    const float M = fmaxf(fmaxf(ms[0], ms[1]), fmaxf(ms[2], ms[3]));
+    float L = 0.f, o = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const float f = expf(ms[w] - M);  // 0 for a wave without tokens
+        L += ls[w] * f;
+        o += os[w][threadIdx.x] * f;
+    }
+    out[((size_t)t * hq + h) * hd + threadIdx.x] = o / L;
 }
 
 void launch_attention(const Dims& D, const BatchView& bv, const SlotBufs& sb, const KVPool& kv,
                       int layer, hipStream_t s) {
-    const int waves = bv.T * D.hq;
-    const int blocks = (waves + 3) / 4;
     if (!D.bf16) {
-        hipLaunchKernelGGL(k_attn_f32, dim3(blocks), dim3(256), 0, s, bv, (const float*)sb.qbuf,
-                           kv, layer, (float*)sb.attn, D.hq, D.hkv, D.hd,
-                           1.0f / sqrtf((float)D.hd));
+        // key rows of a multiple of 4 floats start on 16 bytes (the pool is
+        // 256-byte aligned)
+        const auto fn = D.hd % 4 == 0 ? k_attn_f32<true> : k_attn_f32<false>;
+        hipLaunchKernelGGL(fn, dim3(bv.T * D.hq), dim3(256), 0, s, bv, (const float*)sb.qbuf, kv, layer,
+                           (float*)sb.attn, D.hq, D.hkv, D.hd, 1.0f / sqrtf((float)D.hd));
         return;
     }
     AttnP p;
