@@ -18,6 +18,8 @@
 //     in chunk order (ties to the lowest index) by a second kernel.
 // Merges run in separate launches (stream order makes the partials visible),
 // so no device-scope fence is needed.
+#include <algorithm>
+
 #include "sdv_device.h"
 #include "sdv_internal.h"
 
@@ -27,7 +29,8 @@ static_assert(kVocabChunks <= 64, "chunk partials are merged by one wave");
 struct SampP {
     BatchView bv;
     const float* logits;  // [T][V]
-    int V, cw;            // vocab, chunk width (multiple of 4)
+    int V, cw;            // vocab, chunk width of phase B (multiple of 4)
+    int cwa, chunks_a;    // chunk width and count of phase A
     float* sstat;         // [T][4]
     float* spartA;        // [T][kVocabChunks][4]
     float* spartB;        // [B][kVocabChunks][4]
@@ -40,62 +43,127 @@ struct SampP {
     int groups;
 };
 
-// A1: per (slot, vocab chunk): max, sum of exp(z - max), argmax (lowest index)
-__global__ __launch_bounds__(256) void k_samp_a1(SampP p) {
-    __shared__ float sm[4], ss[4], sv[4];
+// Batch tables of the context-free sampler call, built on the device from
+// the kernel argument (nothing is copied from the host): user ids and draft
+// lengths as given, slot and draft offsets, the (user, slot) of every slot;
+// the error flags are cleared and every draft token is range-checked.  Run by
+// one workgroup of phase A's first kernel, which needs none of them, so the
+// call has no launch of its own for it.
+__device__ __forceinline__ void noalloc_stage(const NoallocMeta& m, const NoallocTables& t, const int32_t* drafts) {
+    __shared__ int so[kNoallocUsers + 1];
+    __shared__ int bad;
+    const int tid = threadIdx.x;
+    if (tid < m.B) {
+        t.user_id[tid] = m.user_id[tid];
+        t.L[tid] = m.L[tid];
+    }
+    if (tid == 0) {
+        bad = 0;
+        int o = 0;
+        for (int b = 0; b < m.B; ++b) {
+            so[b] = o;
+            o += m.L[b] + 1;
+        }
+        so[m.B] = o;
+    }
+    __syncthreads();
+    // a user's drafts start at its slot offset less one slot per earlier user
+    if (tid <= m.B) {
+        t.slot_off[tid] = so[tid];
+        t.draft_off[tid] = so[tid] - tid;
+    }
+    const int T = so[m.B], nd = T - m.B;
+    for (int i = tid; i < T; i += blockDim.x) {
+        int b = 0;
+        while (so[b + 1] <= i) ++b;
+        t.slot_b[i] = b;
+        t.slot_j[i] = i - so[b];
+    }
+    for (int i = tid; i < nd; i += blockDim.x) {
+        const int d = drafts[i];
+        if (d < 0 || d >= m.V) bad = 1;
+    }
+    __syncthreads();
+    if (tid == 0) *t.flags = bad;
+}
+
+// A1: per (slot, vocab chunk): max, sum of exp(z - max), argmax (lowest
+// index).  Bound by the logits' stream.  A thread takes tiles of 16
+// elements (k0 + 4 tid .. in 16-byte loads, or one element every 256 when
+// rows are not 16-byte aligned): their maximum first, then one exponential
+// per element; the workgroup's maximum is known before the sums are merged,
+// so the merge is a rescale and plain sums.  STAGE: the context-free call.
+template <bool STAGE>
+__global__ __launch_bounds__(256) void k_samp_a1(SampP p, NoallocMeta nm, NoallocTables nt) {
+    __shared__ float sm[4], ss[4];
     __shared__ int si[4];
     const int t = blockIdx.x, c = blockIdx.y;
     const float* z = p.logits + (size_t)t * p.V;
-    const int k0 = c * p.cw, k1 = min(p.V, k0 + p.cw);
-    float m = -INFINITY, s = 0.f, bv = -INFINITY;
+    const int k0 = c * p.cwa, k1 = min(p.V, k0 + p.cwa);
+    if (STAGE && t == 0 && c == 0) noalloc_stage(nm, nt, p.bv.drafts);
+    float m = -INFINITY, s = 0.f;  // m: this thread's maximum and, at bi, first argmax
     int bi = 0x7fffffff;
-    auto add = [&](float v, int k) {
-        if (v > bv) { bv = v; bi = k; }  // increasing k per thread: first max kept
-        if (v > m) { s = (m == -INFINITY ? 0.f : s * expf(m - v)) + 1.f; m = v; }
-        else if (v != -INFINITY) s += expf(v - m);
-    };
-    if ((p.V & 3) == 0) {
-        // four float4 loads per thread in flight, then the elements in
-        // increasing k order (chunk bounds are multiples of 4)
-        for (int k4 = k0 + 4 * threadIdx.x; k4 < k1; k4 += 4 * 1024) {
-            float4 v[4];
+    const bool vec = (p.V & 3) == 0 && ((uintptr_t)p.logits & 15) == 0;
+    for (int kt = k0; kt < k1; kt += 4096) {
+        float v[16];
+        // element e of the tile: increasing k per thread
+        auto kof = [&](int e) {
+            return vec ? kt + (e >> 2) * 1024 + 4 * (int)threadIdx.x + (e & 3) : kt + e * 256 + (int)threadIdx.x;
+        };
+        if (vec) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int k = k4 + u * 1024;
-                v[u] = k < k1 ? *(const float4*)(z + k) : float4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+                const int k = kof(4 * u);  // chunk bounds are multiples of 4
+                const float4 f = k < k1 ? *(const float4*)(z + k)
+                                        : float4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+                v[4 * u] = f.x; v[4 * u + 1] = f.y; v[4 * u + 2] = f.z; v[4 * u + 3] = f.w;
             }
+        } else {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int k = k4 + u * 1024;
-                if (k < k1) {
-                    add(v[u].x, k);
-                    add(v[u].y, k + 1);
-                    add(v[u].z, k + 2);
-                    add(v[u].w, k + 3);
-                }
-            }
+            for (int e = 0; e < 16; ++e) v[e] = kof(e) < k1 ? z[kof(e)] : -INFINITY;
         }
-    } else {
-        for (int k = k0 + threadIdx.x; k < k1; k += 256) add(z[k], k);
-    }
+        float mn = m;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const float m2 = __shfl_xor(m, o, 64), s2 = __shfl_xor(s, o, 64);
-        merge_ms(m, s, m2, s2);
-        const float v2 = __shfl_xor(bv, o, 64);
-        const int i2 = __shfl_xor(bi, o, 64);
-        if (v2 > bv || (v2 == bv && i2 < bi)) { bv = v2; bi = i2; }
+        for (int e = 0; e < 16; ++e)
+            if (v[e] > mn) { mn = v[e]; bi = kof(e); }
+        if (mn == -INFINITY) {
+            // nothing but -inf (or NaN, which the sum must show) so far
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                if (v[e] != -INFINITY) s += v[e];
+            continue;
+        }
+        float sum = m == -INFINITY ? s : s * (m == mn ? 1.f : expf(m - mn));
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sum += v[e] == mn ? 1.f : expf(v[e] - mn);
+        s = sum;
+        m = mn;
     }
+    // the wave's maximum and its lowest index, then the sums rescaled to it
+    auto merge = [](float& m, float& s, int& i, float M) {
+        if (m != M) i = 0x7fffffff;
+        if (m != M && m != -INFINITY) s *= expf(m - M);
+        m = M;
+    };
+    merge(m, s, bi, wave_max(m));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) bi = min(bi, __shfl_xor(bi, o, 64));
+    s = wave_sum(s);
     const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) { sm[w] = m; ss[w] = s; sv[w] = bv; si[w] = bi; }
+    if ((threadIdx.x & 63) == 0) { sm[w] = m; ss[w] = s; si[w] = bi; }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int i = 1; i < 4; ++i) {
-            merge_ms(m, s, sm[i], ss[i]);
-            if (sv[i] > bv || (sv[i] == bv && si[i] < bi)) { bv = sv[i]; bi = si[i]; }
+        const float M = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
+        s = 0.f;
+        bi = 0x7fffffff;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            merge(sm[i], ss[i], si[i], M);
+            s += ss[i];
+            bi = min(bi, si[i]);
         }
         float* dst = p.spartA + ((size_t)t * kVocabChunks + c) * 4;
-        dst[0] = m; dst[1] = s; dst[2] = bv; dst[3] = __int_as_float(bi);
+        dst[0] = M; dst[1] = s; dst[2] = M; dst[3] = __int_as_float(bi);
     }
 }
 
@@ -110,11 +178,23 @@ __global__ __launch_bounds__(256) void k_samp_a2(SampP p, int chunks) {
     __shared__ VStat wst[4];
     const int lane = threadIdx.x & 63;
     const BatchView& bv = p.bv;
-    int t;
+    const int t = FUSED ? blockIdx.x : blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (t >= bv.T) return;  // (unfused: a wave past the last slot)
+    // what the accept test reads besides the statistics, requested before the
+    // merge: the draft that follows this slot, its logit and its q
+    const int b = bv.slot_b[t], j = bv.slot_j[t];
+    const bool test = j < bv.L[b];
+    const int di = test ? bv.draft_off[b] + j : 0;
+    int d = test ? bv.drafts[di] : 0;
+    if (d < 0 || d >= p.V) d = 0;  // flagged by the prepare kernel
+    float zdv = 0.f, qd = 0.f;
+    if (test && bv.mode == 1) {
+        zdv = FUSED ? p.zd[t] : p.logits[(size_t)t * p.V + d];
+        if (bv.qk == 0) qd = bv.q[(size_t)di * p.V + d];
+    }
     float M = -INFINITY, S = 0.f;
     int BI = 0x7fffffff;
     if (FUSED) {
-        t = blockIdx.x;
         const VStat* rec = p.lstat + (size_t)t * p.groups;
         VStat a = vstat_empty();
         for (int g0 = 0; g0 < p.groups; g0 += 4 * 256) {
@@ -137,8 +217,6 @@ __global__ __launch_bounds__(256) void k_samp_a2(SampP p, int chunks) {
         for (int w = 1; w < 4; ++w) a = vstat_merge(a, wst[w]);
         M = a.m; S = a.s; BI = a.i;
     } else {
-        t = blockIdx.x * 4 + (threadIdx.x >> 6);
-        if (t >= bv.T) return;
         float BV = -INFINITY;
         if (lane < chunks) {
             const float4 e = *(const float4*)(p.spartA + ((size_t)t * kVocabChunks + lane) * 4);
@@ -154,30 +232,23 @@ __global__ __launch_bounds__(256) void k_samp_a2(SampP p, int chunks) {
         }
     }
     if (BI == 0x7fffffff) BI = 0;  // a row of -inf logits only
-    const int b = bv.slot_b[t], j = bv.slot_j[t];
     // sparse q: q(d) of the draft that follows this slot, looked up by the
     // whole wave (token ids of a row are distinct, so at most one lane hits)
-    float qsp = -1.f;
-    if (bv.qk > 0 && bv.mode == 1 && j < bv.L[b]) {
-        const int di = bv.draft_off[b] + j;
-        const int d = bv.drafts[di];
+    if (bv.qk > 0 && bv.mode == 1 && test) {
+        const int ds = bv.drafts[di];
+        float qsp = -1.f;
         for (int e = lane; e < bv.qk; e += 64)
-            if (bv.q_idx[(size_t)di * bv.qk + e] == d) qsp = bv.q_val[(size_t)di * bv.qk + e];
+            if (bv.q_idx[(size_t)di * bv.qk + e] == ds) qsp = bv.q_val[(size_t)di * bv.qk + e];
         qsp = wave_max(qsp);
-        if (qsp < 0.f) qsp = bv.q_rest[di];
+        qd = qsp < 0.f ? bv.q_rest[di] : qsp;
     }
     if (lane != 0) return;
     float acc = 0.f;
-    if (j < bv.L[b]) {
-        const int di = bv.draft_off[b] + j;
-        int d = bv.drafts[di];
-        if (d < 0 || d >= p.V) d = 0;  // flagged by the prepare kernel
+    if (test) {
         if (bv.mode == 0) acc = (d == BI) ? 1.f : 0.f;
         else if (bv.mode == 2) acc = 1.f;
         else {
-            const float zdv = FUSED ? p.zd[t] : p.logits[(size_t)t * p.V + d];
             const float pd = expf(zdv - M) / S;
-            const float qd = bv.qk > 0 ? qsp : bv.q[(size_t)di * p.V + d];
             const float r = pd / qd;
             float u;
             if (bv.accept_u) u = bv.accept_u[di];
@@ -193,12 +264,18 @@ __global__ __launch_bounds__(256) void k_samp_a2(SampP p, int chunks) {
     st4[0] = M; st4[1] = S; st4[2] = __int_as_float(BI); st4[3] = acc;
 }
 
+// number of leading accepts of user b, by a whole wave: lane j reads slot j's
+// decision (one memory round trip for up to 64 drafts)
 __device__ __forceinline__ int leading_accepts(const SampP& p, int b) {
     const int Lb = p.bv.L[b], so = p.bv.slot_off[b];
     if (p.bv.mode == 2) return Lb;
-    int a = 0;
-    while (a < Lb && p.sstat[(size_t)(so + a) * 4 + 3] != 0.f) ++a;
-    return a;
+    for (int j0 = 0; j0 < Lb; j0 += 64) {
+        const int j = j0 + (int)(threadIdx.x & 63);
+        const bool stop = j >= Lb || p.sstat[(size_t)(so + j) * 4 + 3] == 0.f;
+        const unsigned long long mask = __ballot(stop);
+        if (mask) return min(Lb, j0 + __ffsll(mask) - 1);
+    }
+    return Lb;
 }
 
 // B1 (stochastic): per (user, vocab chunk): best race keys of the residual
@@ -343,52 +420,8 @@ void launch_probs(const Dims& D, const BatchView& bv, const SlotBufs& sb, const 
     hipLaunchKernelGGL(k_probs, dim3(blocks, bv.T), dim3(256), 0, s, bv, logits, sb.sstat, probs, D.V);
 }
 
-// Batch tables of the context-free sampler call, built on the device from
-// the kernel argument (nothing is copied from the host): user ids and draft
-// lengths as given, slot and draft offsets, the (user, slot) of every slot;
-// the error flags are cleared and every draft token is range-checked.  One
-// workgroup of 1024 threads.
-__global__ __launch_bounds__(1024) void k_noalloc_stage(NoallocMeta m, NoallocTables t,
-                                                        const int32_t* drafts) {
-    const int tid = threadIdx.x;
-    if (tid < m.B) {
-        t.user_id[tid] = m.user_id[tid];
-        t.L[tid] = m.L[tid];
-    }
-    if (tid == 0) {
-        int so = 0, dof = 0;
-        for (int b = 0; b < m.B; ++b) {
-            t.slot_off[b] = so;
-            t.draft_off[b] = dof;
-            so += m.L[b] + 1;
-            dof += m.L[b];
-        }
-        t.slot_off[m.B] = so;
-        t.draft_off[m.B] = dof;
-        *t.flags = 0;
-    }
-    __syncthreads();
-    const int T = t.slot_off[m.B], nd = t.draft_off[m.B];
-    for (int i = tid; i < T; i += blockDim.x) {
-        int b = 0;
-        while (t.slot_off[b + 1] <= i) ++b;
-        t.slot_b[i] = b;
-        t.slot_j[i] = i - t.slot_off[b];
-    }
-    __syncthreads();  // flags cleared above before any thread sets a bit
-    for (int i = tid; i < nd; i += blockDim.x) {
-        const int d = drafts[i];
-        if (d < 0 || d >= m.V) atomicOr(t.flags, 1);
-    }
-}
-
-void launch_noalloc_stage(const NoallocMeta& m, const NoallocTables& t, const int32_t* drafts,
-                          hipStream_t s) {
-    hipLaunchKernelGGL(k_noalloc_stage, dim3(1), dim3(1024), 0, s, m, t, drafts);
-}
-
 void launch_sampler(const Dims& D, const BatchView& bv, const SlotBufs& sb, const float* logits,
-                    hipStream_t s, int groups) {
+                    hipStream_t s, int groups, const NoallocMeta* nm, const NoallocTables* nt) {
     SampP p;
     p.bv = bv;
     p.logits = logits;
@@ -406,8 +439,18 @@ void launch_sampler(const Dims& D, const BatchView& bv, const SlotBufs& sb, cons
     if (groups > 0) {
         hipLaunchKernelGGL(k_samp_a2<true>, dim3(bv.T), dim3(256), 0, s, p, chunks);
     } else {
-        hipLaunchKernelGGL(k_samp_a1, dim3(bv.T, chunks), dim3(256), 0, s, p);
-        hipLaunchKernelGGL(k_samp_a2<false>, dim3((bv.T + 3) / 4), dim3(256), 0, s, p, chunks);
+        // phase A chunks: about 4096 workgroups in all (each pays its merge,
+        // 64 chunks a slot cost 32 us for 108 slots of 151936 against 15),
+        // at least one 4096-element tile each
+        const int ca = std::max(1, std::min(std::min(kVocabChunks, (4096 + bv.T - 1) / bv.T), (D.V + 4095) / 4096));
+        p.cwa = ((D.V + ca - 1) / ca + 3) & ~3;
+        p.chunks_a = (D.V + p.cwa - 1) / p.cwa;
+        const dim3 ga(bv.T, p.chunks_a);
+        if (nm)
+            hipLaunchKernelGGL(k_samp_a1<true>, ga, dim3(256), 0, s, p, *nm, *nt);
+        else
+            hipLaunchKernelGGL(k_samp_a1<false>, ga, dim3(256), 0, s, p, NoallocMeta{}, NoallocTables{});
+        hipLaunchKernelGGL(k_samp_a2<false>, dim3((bv.T + 3) / 4), dim3(256), 0, s, p, p.chunks_a);
     }
     if (bv.mode == 1) {
         if (bv.qk > 0)

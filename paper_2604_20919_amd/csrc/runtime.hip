@@ -1233,8 +1233,7 @@ sd_status sd_sample_logits_noalloc(int32_t n_users, const int32_t* user_ids, con
     Dims D{};
     D.V = vocab;
     hipStream_t st = (hipStream_t)stream;
-    launch_noalloc_stage(meta, t, draft_tokens, st);
-    launch_sampler(D, bv, sb, logits, st);
+    launch_sampler(D, bv, sb, logits, st, 0, &meta, &t);
     return hip_status(hipGetLastError());
 }
 

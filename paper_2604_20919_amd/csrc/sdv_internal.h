@@ -183,8 +183,13 @@ void launch_pack(const void* s0, const void* s1, const void* s2, int seg1, int s
 // Accept/resample of a batch.  groups = 0: phase A over the logits; groups
 // > 0: phase A from the lm_head epilogue's statistics (sb.lstat, groups
 // partials per slot, and sb.zd); logits then only feed phase B (stochastic).
+// nm / nt (context-free call, groups = 0): the batch tables are built by
+// phase A's first kernel.
+struct NoallocMeta;
+struct NoallocTables;
 void launch_sampler(const Dims& D, const BatchView& bv, const SlotBufs& sb, const float* logits,
-                    hipStream_t s, int groups = 0);
+                    hipStream_t s, int groups = 0, const NoallocMeta* nm = nullptr,
+                    const NoallocTables* nt = nullptr);
 // probs[t][k] = exp(z[t][k] - m_t) / S_t from the sampler's per-slot
 // statistics (the same expression the race uses for p)
 void launch_probs(const Dims& D, const BatchView& bv, const SlotBufs& sb, const float* logits,
@@ -209,9 +214,6 @@ struct NoallocMeta {  // kernel argument (520 bytes)
 struct NoallocTables {  // device pointers into the scratch array
     int32_t *user_id, *L, *slot_off, *draft_off, *slot_b, *slot_j, *flags;
 };
-void launch_noalloc_stage(const NoallocMeta& m, const NoallocTables& t, const int32_t* drafts,
-                          hipStream_t s);
-
 void launch_kv_copy(const Dims& D, const KVPool& kv, const KVCopyPages& pages, int layer,
                     int pos0, int n, const void* k, const void* v, int to_pool, hipStream_t s);
 
