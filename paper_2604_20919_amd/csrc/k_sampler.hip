@@ -280,13 +280,24 @@ __device__ __forceinline__ int leading_accepts(const SampP& p, int b) {
 
 // B1 (stochastic): per (user, vocab chunk): best race keys of the residual
 // max(0, p - q) at the stop slot and of p itself (the bonus draw, and the
-// fallback when the residual is empty); both use the same unit exponentials
+// fallback when the residual is empty); both use the same unit exponentials.
+// Bound by the vector units (Philox, exp, log1p, divisions) and, for few users,
+// by the chain of loads before them (launch_sampler picks the width).
+// A key w / E needs a logarithm and a division, and few elements can win:
+// V <= E <= V / (1 - V) bounds it from both sides at the price of a
+// reciprocal.  Per tile: the workgroup's largest lower bound of each race,
+// then the exact key of the elements whose upper bound reaches it (the
+// winner's does, and so does every tie's).  The factors cover the rounding
+// of the bounds and of log1pf (a few 2^-23), the added terms that of
+// subnormal keys.  (Every key exact, 256 threads: 1 / 16 / 32 users of 151936
+// tokens 11.2 / 23.9 / 44.2 us; this 9.7 / 20.6 / 37.8.)
 template <bool SPARSE>
-__global__ __launch_bounds__(256) void k_samp_b1(SampP p) {
-    __shared__ float sk[2][4];
-    __shared__ int sidx[2][4];
+__global__ __launch_bounds__(1024) void k_samp_b1(SampP p) {
+    __shared__ float sk[2][16], sl[2][16];
+    __shared__ int sidx[2][16];
     __shared__ float qloc[SPARSE ? kSparseChunkMax : 1];  // sparse q over this chunk
     const int b = blockIdx.x, c = blockIdx.y;
+    const int nt = blockDim.x, w = threadIdx.x >> 6, nw = nt >> 6, lane = threadIdx.x & 63;
     const BatchView& bv = p.bv;
     const int Lb = bv.L[b];
     const int a = leading_accepts(p, b);
@@ -303,9 +314,9 @@ __global__ __launch_bounds__(256) void k_samp_b1(SampP p) {
         if (resid) {
             const size_t di = (size_t)bv.draft_off[b] + a;
             const float rest = bv.q_rest[di];
-            for (int k = threadIdx.x; k < k1 - k0; k += 256) qloc[k] = rest;
+            for (int k = threadIdx.x; k < k1 - k0; k += nt) qloc[k] = rest;
             __syncthreads();
-            for (int e = threadIdx.x; e < bv.qk; e += 256) {
+            for (int e = threadIdx.x; e < bv.qk; e += nt) {
                 const int tk = bv.q_idx[di * bv.qk + e];
                 if (tk >= k0 && tk < k1) qloc[tk - k0] = bv.q_val[di * bv.qk + e];
             }
@@ -315,28 +326,52 @@ __global__ __launch_bounds__(256) void k_samp_b1(SampP p) {
         qr = resid ? bv.q + (size_t)(bv.draft_off[b] + a) * p.V : nullptr;
     }
     const uint64_t user = (uint64_t)bv.user_id[b];
+    constexpr float kUp = 1.f + 0x1p-18f, kDown = 1.f - 0x1p-18f, kTiny = 1e-37f;
     float br = -1.f, bp = -1.f;
     int ir = 0x7fffffff, ip = 0x7fffffff;
-    for (int k4 = k0 + 4 * threadIdx.x; k4 < k1; k4 += 4 * 256) {
-        const u64x4 ctr = {bv.round, user, ((uint64_t)PURPOSE_RACE << 32) | (uint64_t)a,
-                           (uint64_t)(k4 >> 2)};
-        const u64x4 rnd = philox4x64_10(ctr, bv.seed, 0ull);
+    float tp = 0.f, tr = 0.f;  // largest lower bounds so far
+    for (int kt = k0; kt < k1; kt += 4 * nt) {
+        const int k4 = kt + 4 * (int)threadIdx.x;
+        float pk[4], wk[4], vv[4];
+        float lp = 0.f, lr = 0.f;
+        u64x4 rnd = u64x4{0, 0, 0, 0};
+        if (k4 < k1) {
+            const u64x4 ctr = {bv.round, user, ((uint64_t)PURPOSE_RACE << 32) | (uint64_t)a, (uint64_t)(k4 >> 2)};
+            rnd = philox4x64_10(ctr, bv.seed, 0ull);
+        }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int k = k4 + e;
-            if (k >= k1) break;
-            const float pk = expf(z[k] - M) / S;
-            const float E = race_exponential(word_of(rnd, e));
-            if (pk > 0.f) {
-                const float kp = pk / E;
-                if (kp > bp) { bp = kp; ip = k; }
-            }
-            if (resid) {
-                const float wk = fmaxf(pk - (SPARSE ? qloc[k - k0] : qr[k]), 0.f);
-                if (wk > 0.f) {
-                    const float kr = wk / E;
-                    if (kr > br) { br = kr; ir = k; }
-                }
+            const bool on = k < k1;
+            pk[e] = on ? expf(z[k] - M) / S : 0.f;
+            wk[e] = on && resid ? fmaxf(pk[e] - (SPARSE ? qloc[k - k0] : qr[k]), 0.f) : 0.f;
+            vv[e] = race_uniform(word_of(rnd, e));
+            const float low = (1.f - vv[e]) * __builtin_amdgcn_rcpf(vv[e]);
+            if (pk[e] > 0.f) lp = fmaxf(lp, pk[e] * low);
+            if (wk[e] > 0.f) lr = fmaxf(lr, wk[e] * low);
+        }
+        lp = wave_max(lp);
+        lr = wave_max(lr);
+        if (kt > k0) __syncthreads();  // the previous tile's bounds have been read
+        if (lane == 0) { sl[0][w] = lp; sl[1][w] = lr; }
+        __syncthreads();
+        for (int i = 0; i < nw; ++i) {
+            lp = fmaxf(lp, sl[0][i]);
+            lr = fmaxf(lr, sl[1][i]);
+        }
+        tp = fmaxf(tp, fmaf(lp, kDown, -kTiny));
+        tr = fmaxf(tr, fmaf(lr, kDown, -kTiny));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float up = kUp * __builtin_amdgcn_rcpf(vv[e]);
+            const bool np = pk[e] > 0.f && fmaf(pk[e], up, kTiny) >= tp;
+            const bool nr = wk[e] > 0.f && fmaf(wk[e], up, kTiny) >= tr;
+            if (np || nr) {
+                const float E = -log1pf(-vv[e]);
+                const float kp = pk[e] / E;
+                if (np && kp > bp) { bp = kp; ip = k4 + e; }
+                const float kr = wk[e] / E;
+                if (nr && kr > br) { br = kr; ir = k4 + e; }
             }
         }
     }
@@ -349,11 +384,10 @@ __global__ __launch_bounds__(256) void k_samp_b1(SampP p) {
         const int j2 = __shfl_xor(ip, o, 64);
         if (p2 > bp || (p2 == bp && j2 < ip)) { bp = p2; ip = j2; }
     }
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) { sk[0][w] = br; sidx[0][w] = ir; sk[1][w] = bp; sidx[1][w] = ip; }
+    if (lane == 0) { sk[0][w] = br; sidx[0][w] = ir; sk[1][w] = bp; sidx[1][w] = ip; }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int i = 1; i < 4; ++i) {
+        for (int i = 1; i < nw; ++i) {
             if (sk[0][i] > br || (sk[0][i] == br && sidx[0][i] < ir)) { br = sk[0][i]; ir = sidx[0][i]; }
             if (sk[1][i] > bp || (sk[1][i] == bp && sidx[1][i] < ip)) { bp = sk[1][i]; ip = sidx[1][i]; }
         }
@@ -453,10 +487,15 @@ void launch_sampler(const Dims& D, const BatchView& bv, const SlotBufs& sb, cons
         hipLaunchKernelGGL(k_samp_a2<false>, dim3((bv.T + 3) / 4), dim3(256), 0, s, p, p.chunks_a);
     }
     if (bv.mode == 1) {
+        // whole waves, as many as are resident at once over all users (24 a
+        // CU), each thread taking the same number of four-element tiles
+        const int quads = p.cw / 4, most = std::min(16, std::max(1, 24 * 256 / (bv.B * chunks))) * 64;
+        const int tiles = (quads + most - 1) / most;
+        const int nt = ((quads + tiles - 1) / tiles + 63) & ~63;
         if (bv.qk > 0)
-            hipLaunchKernelGGL(k_samp_b1<true>, dim3(bv.B, chunks), dim3(256), 0, s, p);
+            hipLaunchKernelGGL(k_samp_b1<true>, dim3(bv.B, chunks), dim3(nt), 0, s, p);
         else
-            hipLaunchKernelGGL(k_samp_b1<false>, dim3(bv.B, chunks), dim3(256), 0, s, p);
+            hipLaunchKernelGGL(k_samp_b1<false>, dim3(bv.B, chunks), dim3(nt), 0, s, p);
     }
     hipLaunchKernelGGL(k_samp_b2, dim3((bv.B + 3) / 4), dim3(256), 0, s, p, chunks);
 }

@@ -167,17 +167,12 @@ __device__ __forceinline__ float accept_uniform(uint64_t x) {
     return static_cast<float>(static_cast<uint32_t>(x >> 40)) * 0x1.0p-24f;
 }
 
-// V in [2^-64, 1): the 24 bits below the leading one, scaled by its position
+// V in [2^-64, 1) of the unit exponential -log1p(-V): the 24 bits below the leading one, scaled by its position
 __device__ __forceinline__ float race_uniform(uint64_t x) {
     if (x == 0) return 0.0f;
     const int lz = __clzll(static_cast<long long>(x));
     const uint32_t mant = static_cast<uint32_t>((x << lz) >> 40);
     return ldexpf(static_cast<float>(mant), -24 - lz);
-}
-
-// unit exponential -log(1 - V)
-__device__ __forceinline__ float race_exponential(uint64_t x) {
-    return -log1pf(-race_uniform(x));
 }
 
 }  // namespace sdv
