@@ -146,9 +146,19 @@ __device__ __forceinline__ float rstd_of(const GemmP& p, const float (&v)[kNormK
 }
 __device__ __forceinline__ float row_rstd(const GemmP& p, int t) {
     if (p.nss == nullptr) return 1.0f;
-    float v[kNormKMax / kNormBlock];
-    load_row_ss(p, t, true, v);
-    return rstd_of(p, v);
+    float ss = 0.f;
+    for (int b = 0; b < p.nnb; ++b) ss += p.nss[(size_t)t * p.nnb + b];
+    return 1.0f / sqrtf(ss / (float)p.K + p.eps);
+}
+// block sums that do not fit a thread's registers (the few-slot products
+// write one per 16 columns): one wave per slot, lanes over the blocks
+template <int NW>
+__device__ __forceinline__ void row_factors_by_wave(const GemmP& p, float* rsl, int tb, int nsl) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int sl = wave; sl < nsl && tb + sl < p.T; sl += NW) {
+        const float ss = lane_blocks_sum(p.nss + (size_t)(tb + sl) * p.nnb, p.nnb, lane);
+        if (lane == 0) rsl[sl] = 1.0f / sqrtf(ss / (float)p.K + p.eps);
+    }
 }
 
 __device__ __forceinline__ float silu(float g) { return g / (1.0f + expf(-g)); }
@@ -362,6 +372,10 @@ void k_gemm16(GemmP p) {
         for (int i = 0; i < NSPT; ++i) {
             const int sl = threadIdx.x + i * NTH;
             if (sl < NSL) rsl[sl] = p.nss != nullptr ? rstd_of(p, ssv[i]) : 1.0f;
+        }
+        if (p.nss != nullptr && p.nnb > kNormKMax / kNormBlock) {
+            __syncthreads();
+            row_factors_by_wave<NW>(p, rsl, 0, NSL);
         }
     }
     store_x(xr[0], 0);
@@ -750,6 +764,10 @@ void k_gemm32(GemmP p) {
             const int sl = threadIdx.x + i * NTH;
             if (sl < NSL) rsl[sl] = p.nss != nullptr ? rstd_of(p, ssv[i]) : 1.0f;
         }
+        if (p.nss != nullptr && p.nnb > kNormKMax / kNormBlock) {
+            __syncthreads();
+            row_factors_by_wave<NW>(p, rsl, tb, NSL);
+        }
     }
     // When a chunk starts its X has landed, and the weight loads issued after
     // those direct loads may be in flight (loads retire in order).
@@ -985,6 +1003,190 @@ void k_gemm32(GemmP p) {
     }
 }
 
+// ---------------------------------------------------------------------------
+// Few slots (at most 16) against a matrix of few 16-row groups: a drafting
+// model's decode step.  Such a product is a few MB to a few tens of MB of
+// weights, a handful of microseconds of HBM time, and what it takes is the
+// number of dependent memory round trips; so a workgroup owns NG whole
+// 16-row groups, its waves share the k range and request their whole share
+// (U fragments of 1 KB per group and step, two steps in flight) before the
+// first product, the B operand comes straight from the activation rows (they
+// sit in L2; no staging, no barrier in the loop), and the waves' sums meet in
+// LDS, so that the epilogue follows in the same launch: no partial planes, no
+// reduction kernel.
+//   RAW     one plane of raw sums for k_qkrope_bf16
+//   SWIGLU  two groups, gate and up
+//   RESID   x += sum, h = x * gamma and one sum of squares per workgroup's columns
+// PACK (at most 8 slots): columns 0-7 of the B operand are the slots' hi plane
+// and 8-15 their lo plane, one load and one MFMA instead of two.
+// Qwen3-1.7B, one slot, us a product with its reduction: QKV 7.4 -> 5.6, O
+// 6.1 + 2.8 -> 5.7, gate/up 13.6 + 3.8 -> 11.9, down 6.1 + 2.8 -> 8.7 (whole
+// 16-row groups: 10.3); the step 1685 -> 1421.
+// HALF: a workgroup takes 8 rows of a group (the other lanes of the A operand
+// are zero), twice the workgroups where whole groups leave half the CUs idle.
+// ---------------------------------------------------------------------------
+enum { FEW_RAW = 0, FEW_SWIGLU = 1, FEW_RESID = 2 };
+struct FewP {
+    const bf16_t* X;   // [2][T][K]
+    const bf16_t* Wp;  // packed, [groups][K/32][64][8]
+    int K, KT, T, N;   // N: output columns
+    int groups;
+    float* out;        // RAW: [T][N]
+    bf16_t* act;       // SWIGLU: [2][T][N]
+    const float* nss;  // SWIGLU: block sums of squares of the input rows
+    int nnb;
+    float eps;
+    float* x;          // RESID: [T][N], gamma [N], h [2][T][N], ssq [T][workgroups]
+    const bf16_t* gamma;
+    bf16_t* h;
+    float* ssq;
+};
+
+template <int NW, int EPI, bool PACK, bool HALF>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void k_gemm_few(FewP p) {
+    static_assert(!HALF || EPI != FEW_SWIGLU, "half groups: one group per workgroup");
+    constexpr int ROWS = HALF ? 8 : 16;            // output columns per workgroup
+    constexpr int NG = EPI == FEW_SWIGLU ? 2 : 1;  // 16-row groups
+    constexpr int PL = PACK ? 1 : 2;               // B operands per fragment
+    constexpr int U = NG == 2 && !PACK ? 2 : 4;    // fragments per wave and step
+    constexpr int LDG = 64 * 4 + 3 * 16;           // staged group (16 floats between the row quads)
+    __shared__ float red[NW][NG * LDG];
+    __shared__ float rsl[16];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int lr = lane & 15, lg = lane >> 4;
+    const int wv = __builtin_amdgcn_readfirstlane(wave);
+    const int g0 = HALF ? blockIdx.x >> 1 : blockIdx.x * NG;
+    const int r0 = HALF ? (blockIdx.x & 1) * 8 : 0;  // first row of the group
+
+    // epilogue inputs, requested ahead of the weights: output (slot te, row
+    // r0 + ne) of a group is thread te * ROWS + ne's
+    const int te = threadIdx.x / ROWS, ne = threadIdx.x % ROWS;
+    const bool mine = te < p.T;
+    const int col = blockIdx.x * ROWS + ne;
+    uint32_t xin = 0;
+    uint16_t gin = 0;
+    if constexpr (EPI == FEW_RESID) {
+        const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(p.x, (short)0, p.T * p.N * 4, 0x00020000);
+        const __amdgpu_buffer_rsrc_t gr =
+            __builtin_amdgcn_make_buffer_rsrc((void*)p.gamma, (short)0, p.N * 2, 0x00020000);
+        xin = __builtin_amdgcn_raw_buffer_load_b32(xr, mine ? (te * p.N + col) * 4 : (int)0x80000000u, 0, 0);
+        gin = __builtin_amdgcn_raw_buffer_load_b16(gr, col * 2, 0, 0);
+    }
+    constexpr int SPW = ((PACK ? 8 : 16) + NW - 1) / NW;  // slots per wave
+    f32x4 ssv[SPW][2];
+    if constexpr (EPI == FEW_SWIGLU) {
+#pragma unroll
+        for (int i = 0; i < SPW; ++i) row_blocks_load(p.nss, p.T, p.nnb, wv + i * NW, lane, ssv[i]);
+    }
+
+    const uint64_t wbytes = (uint64_t)p.groups * (uint64_t)p.KT * 1024u;
+    const int wrec = (int)(wbytes > 0x7fffffffu ? 0x7fffffffu : wbytes), xrec = 2 * p.T * p.K * 2;
+    uint32_t woff[NG], xoff[PL];
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+        woff[g] = HALF && (lr & 8) != r0 ? 0x80000000u
+                                         : (uint32_t)(g0 + g) * (uint32_t)p.KT * 1024u + (uint32_t)lane * 16u;
+#pragma unroll
+    for (int pl = 0; pl < PL; ++pl) {
+        const int slot = PACK ? lr & 7 : lr, plane = PACK ? lr >> 3 : pl;
+        // columns without a slot point past the buffer and read as zero
+        xoff[pl] = slot < p.T ? ((uint32_t)(plane * p.T + slot) * (uint32_t)p.K + 8u * (uint32_t)lg) * 2u : 0x80000000u;
+    }
+    bf16x8 w[2][U][NG], x[2][U][PL];
+    // step s of this wave: fragments s * NW * U + wv * U .. + U - 1 (KT is a
+    // multiple of U); steps past the end read an empty resource
+    auto load = [&](bf16x8 (&ww)[U][NG], bf16x8 (&xx)[U][PL], int s) {
+        const int f = (s * NW + wv) * U;
+        const bool on = f < p.KT;
+        const __amdgpu_buffer_rsrc_t wres =
+            __builtin_amdgcn_make_buffer_rsrc((void*)p.Wp, (short)0, on ? wrec : 0, 0x00020000);
+        const __amdgpu_buffer_rsrc_t xres =
+            __builtin_amdgcn_make_buffer_rsrc((void*)p.X, (short)0, on ? xrec : 0, 0x00020000);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int g = 0; g < NG; ++g)
+                ww[u][g] = __builtin_bit_cast(
+                    bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wres, woff[g], (f + u) * 1024, kWeightAux));
+#pragma unroll
+            for (int pl = 0; pl < PL; ++pl)
+                xx[u][pl] = __builtin_bit_cast(
+                    bf16x8, __builtin_amdgcn_raw_buffer_load_b128(xres, xoff[pl], (f + u) * 64, 0));
+        }
+    };
+    f32x4 acc[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int steps = (p.KT + NW * U - 1) / (NW * U);
+    load(w[0], x[0], 0);
+    load(w[1], x[1], 1);
+    __builtin_amdgcn_sched_barrier(0);
+    for (int s0 = 0; s0 < steps; s0 += 2) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int pl = 0; pl < PL; ++pl)
+#pragma unroll
+                    for (int g = 0; g < NG; ++g)
+                        acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[b][u][g], x[b][u][pl], acc[g], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (s0 + 2 < steps) load(w[b], x[b], s0 + b + 2);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    // lane holds rows 4 * lg + e of column lr
+#pragma unroll
+    for (int g = 0; g < NG; ++g) *(f32x4*)&red[wave][g * LDG + lane * 4 + lg * 16] = acc[g];
+    if constexpr (EPI == FEW_SWIGLU) {
+#pragma unroll
+        for (int i = 0; i < SPW; ++i) {
+            const float ss = row_blocks_sum(ssv[i], p.nnb, lane);
+            if (lane == 0 && wv + i * NW < 16) rsl[wv + i * NW] = 1.0f / sqrtf(ss / (float)p.K + p.eps);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x >= 16 * ROWS) return;
+    // sums of (slot te, row r0 + ne) in wave order
+    float v[NG];
+    const int o = te * 4 + ((r0 + ne) >> 2) * 80 + (ne & 3);
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        float a = 0.f;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) a += red[q][g * LDG + o];
+        if constexpr (PACK) {
+            float lo = 0.f;
+            if (te < 8) {
+#pragma unroll
+                for (int q = 0; q < NW; ++q) lo += red[q][g * LDG + o + 32];
+            }
+            a += lo;
+        }
+        v[g] = a;
+    }
+    if constexpr (EPI == FEW_RAW) {
+        if (mine) p.out[(size_t)te * p.N + col] = v[0];
+    } else if constexpr (EPI == FEW_SWIGLU) {
+        if (mine) {
+            const float sc = rsl[te];
+            st_act(p.act, (size_t)p.T * p.N, (size_t)te * p.N + col, silu(v[0] * sc) * (v[1 % NG] * sc));
+        }
+    } else {
+        const float r = __uint_as_float(xin) + v[0];
+        if (mine) {
+            p.x[(size_t)te * p.N + col] = r;
+            st_act(p.h, (size_t)p.T * p.N, (size_t)te * p.N + col, r * bf16_to_f32(gin));
+        }
+        float ss = r * r;
+#pragma unroll
+        for (int d = ROWS / 2; d > 0; d >>= 1) ss += __shfl_xor(ss, d, ROWS);
+        if (mine && ne == 0) p.ssq[(size_t)te * (p.N / ROWS) + blockIdx.x] = ss;
+    }
+}
+
 // Sum of the S split-K partials (in split order) plus the epilogue; one
 // thread per 4 output columns of one slot.
 template <int EPI>
@@ -1157,7 +1359,7 @@ static int cu_count();
 static GemmShape shape_for(int T, int vcols, bool raw, int K) {
     const bool wide = vcols % 256 == 0;
     constexpr int kT32 = 97;  // slot counts the 16x16 form's tiles end at
-    const GemmShape g16{16, std::max(2, (T + 15) / 16), 4, 1, 1, 64, 32, 0};
+    const GemmShape g16{16, (T + 15) / 16, 4, 1, 1, 64, 32, 0};
     if (T < kT32) {
         // split-K partial GEMMs with few weight rows (the Qwen3-1.7B shapes):
         // when 256-row workgroups with at least two 128-k chunks per split
@@ -1224,6 +1426,7 @@ static GemmFn pick32(bool split, int epi, bool skf) {
 static GemmFn pick(const GemmShape& sh, bool split, int epi, bool skf = false) {
     if (sh.F == 16) {
         switch (sh.MT) {
+            case 1: return pick16<1>(split, epi);
             case 2: return pick16<2>(split, epi);
             case 3: return pick16<3>(split, epi);
             case 4: return pick16<4>(split, epi);
@@ -1246,6 +1449,7 @@ static GemmFn pick(const GemmShape& sh, bool split, int epi, bool skf = false) {
 static GemmFn pick_la(const GemmShape& sh) {
     if (sh.F != 16) return nullptr;
     switch (sh.MT) {
+        case 1: return k_gemm16<1, 2, 64, EPI_SWIGLU, false, 4, 2, 2, 16, true>;
         case 2: return k_gemm16<2, 2, 64, EPI_SWIGLU, false, 4, 2, 2, 16, true>;
         case 3: return k_gemm16<3, 2, 64, EPI_SWIGLU, false, 4, 2, 2, 16, true>;
         case 4: return k_gemm16<4, 2, 64, EPI_SWIGLU, false, 4, 2, 2, 16, true>;
@@ -1313,6 +1517,55 @@ size_t gemm_partial_floats(const Dims& D, int Tmax) {
 }
 
 
+// Few-slot products.  PACK needs at most 8 slots; unpacked, an activation
+// fragment is twice a weight fragment, so only the gate/up product, which
+// shares it between two groups, still reads no more activations than weights.
+// (14 slots: gate/up 16.2 -> 15.5 us; the others 8.2-15.6 against 7.5-9.9.)
+// The workgroups must all be resident at once (two eight-wave ones or one
+// sixteen-wave one per CU): with more (the Qwen3-32B projections) the tiled
+// forms' split k is faster (8 slots, 16 layers: 3370 against 3900 us).  Returns 0 when another form takes the call, else
+// the columns of a workgroup.
+static int try_few(const Dims& D, const GemmCall& g, const SlotBufs& sb, hipStream_t s) {
+    const bool swiglu = g.epi == EPI_SWIGLU;
+    if (g.T > (swiglu ? 16 : 8) || g.K % 128 || g.N % 16 || g.epi == EPI_LMSTAT) return 0;
+    if (swiglu ? g.norm_ss == nullptr || g.norm_nb > kFewBlocks || g.ldo != g.N : !g.raw) return 0;
+    int wgs = g.N / 16;
+    if (wgs > (swiglu ? 2 : 1) * cu_count()) return 0;
+    const bool half = !swiglu && 2 * wgs <= cu_count();
+    if (half) wgs *= 2;
+    FewP p{};
+    p.X = (const bf16_t*)g.X;
+    p.Wp = (const bf16_t*)g.Wp;
+    p.K = g.K;
+    p.KT = g.K / 32;
+    p.T = g.T;
+    p.N = g.N;
+    p.groups = (swiglu ? 2 : 1) * (g.N / 16);
+    p.eps = D.eps;
+    if (swiglu) {
+        p.act = (bf16_t*)g.out;
+        p.nss = g.norm_ss;
+        p.nnb = g.norm_nb;
+        const auto fn = g.T <= 8 ? k_gemm_few<8, FEW_SWIGLU, true, false> : k_gemm_few<8, FEW_SWIGLU, false, false>;
+        hipLaunchKernelGGL(fn, dim3(wgs), dim3(512), 0, s, p);
+        return 16;
+    }
+    const bool resid = g.res_gamma && wgs <= kFewBlocks;
+    if (resid) {
+        p.x = sb.x;
+        p.gamma = (const bf16_t*)g.res_gamma;
+        p.h = (bf16_t*)sb.h;
+        p.ssq = sb.ssq;
+    } else {
+        if (g.res_gamma) return 0;
+        p.out = sb.gpart;
+    }
+    const auto fn = resid ? (half ? k_gemm_few<16, FEW_RESID, true, true> : k_gemm_few<16, FEW_RESID, true, false>)
+                          : (half ? k_gemm_few<16, FEW_RAW, true, true> : k_gemm_few<16, FEW_RAW, true, false>);
+    hipLaunchKernelGGL(fn, dim3(wgs), dim3(1024), 0, s, p);
+    return half ? 8 : 16;
+}
+
 int launch_gemm(const Dims& D, const GemmCall& g, const SlotBufs& sb, hipStream_t s) {
     if (!D.bf16) {
         GemmF p;
@@ -1335,6 +1588,7 @@ int launch_gemm(const Dims& D, const GemmCall& g, const SlotBufs& sb, hipStream_
         hipLaunchKernelGGL(fn, dim3((g.N + 15) / 16, (g.T + 15) / 16), dim3(256), 0, s, p);
         return 1;
     }
+    if (const int cols = try_few(D, g, sb, s)) return g.res_gamma ? -cols : 1;
     const int vcols = g.epi == EPI_SWIGLU ? 2 * g.N : g.N;
     const GemmShape sh = shape_for(g.T, vcols, g.raw != 0, g.K);
     GemmP p;

@@ -411,10 +411,15 @@ __global__ __launch_bounds__(64) void k_qkrope_bf16(BatchView bv, const float* q
     const int nqkv = nh * HD;
     const size_t plane = (size_t)bv.T * nqkv;
     const float* src = qkv + (size_t)t * nqkv + (size_t)h * HD + 4 * l;
+    // block sums of the input's RMSNorm: every lane all of them, or (one per
+    // few columns, at most kFewBlocks) lanes over the blocks
+    const bool many = nnb > kNormKMax / kNormBlock;
     float ssb[kNormKMax / kNormBlock];
 #pragma unroll
     for (int b = 0; b < kNormKMax / kNormBlock; ++b)
-        ssb[b] = nss != nullptr && b < nnb ? nss[(size_t)t * nnb + b] : 0.f;
+        ssb[b] = nss != nullptr && !many && b < nnb ? nss[(size_t)t * nnb + b] : 0.f;
+    f32x4 ssm[2];
+    row_blocks_load(nss, many ? bv.T : 0, nnb, t, lane, ssm);
     // partial planes added in split order, eight planes' loads in flight
     f32x4 xa = f32x4{0.f, 0.f, 0.f, 0.f}, xb = xa;
     for (int sp = 0; sp < S; sp += 8) {
@@ -437,6 +442,7 @@ __global__ __launch_bounds__(64) void k_qkrope_bf16(BatchView bv, const float* q
         float ssx = 0.f;
 #pragma unroll
         for (int b = 0; b < kNormKMax / kNormBlock; ++b) ssx += ssb[b];
+        if (many) ssx = row_blocks_sum(ssm, nnb, lane);
         const float rt = 1.0f / sqrtf(ssx / (float)d + eps);
         xa *= rt;
         xb *= rt;
@@ -500,14 +506,14 @@ __global__ __launch_bounds__(64) void k_qkrope_bf16(BatchView bv, const float* q
 }
 
 void launch_qkv_finish(const Dims& D, const BatchView& bv, const SlotBufs& sb, const KVPool& kv,
-                       int layer, const float* part, int S, const void* qn, const void* kn,
+                       int layer, const float* part, int S, int nnb, const void* qn, const void* kn,
                        hipStream_t s) {
     if (D.bf16) {
         // head_dim 128 (checked at init): four heads per wave
         const int waves = bv.T * ((D.hq + 2 * D.hkv + 3) / 4);
         hipLaunchKernelGGL(k_qkrope_bf16, dim3(waves), dim3(64), 0, s, bv, part, S, sb.cs,
                            (bf16_t*)sb.qbuf, kv, layer, (const bf16_t*)qn, (const bf16_t*)kn, D.hq,
-                           D.hkv, D.qk_norm, D.eps, sb.ssq, sb.nsq, D.d);
+                           D.hkv, D.qk_norm, D.eps, sb.ssq, nnb, D.d);
         return;
     }
     const int waves = bv.T * (D.hq + D.hkv);

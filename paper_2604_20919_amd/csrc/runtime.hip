@@ -134,7 +134,8 @@ Layout plan(const sd_config& c) {
     L.cs = take((size_t)L.Tmax * (D.hd / 2) * 2 * 4);
     L.x = take((size_t)L.Tmax * D.d * 4);
     L.nsq = (D.d + kNormBlock - 1) / kNormBlock;
-    L.ssq = take((size_t)L.Tmax * L.nsq * 4);
+    // (few-slot products write up to kFewBlocks sums a row of at most 8 slots)
+    L.ssq = take(std::max((size_t)L.Tmax * L.nsq, (size_t)std::min(L.Tmax, 8) * kFewBlocks) * 4);
     // activations that feed matrix products: two bf16 planes (hi, lo) each
     // in the bf16 configuration, one fp32 plane otherwise
     const size_t ap = D.bf16 ? 2 : 1;
@@ -441,6 +442,7 @@ sd_status enqueue_forward(sd_ctx* c, Slot& s, const BatchView& bv, hipStream_t s
         // gain (bf16: h = x * gain and the block sums of squares)
         launch_embed_norm(D, bv, c->w.embed, c->layers[0].norm1, sb, st);
     }
+    int nnb = sb.nsq;  // block sums of squares per row of x
     // GEMM input RMSNorm(x) * gamma: h = RMSNorm(x) * gamma (fp32), or
     // h = x * gamma with the rstd factor applied to the GEMM's outputs (bf16:
     // the norm's row reduction then needs no single-workgroup pass)
@@ -448,12 +450,15 @@ sd_status enqueue_forward(sd_ctx* c, Slot& s, const BatchView& bv, hipStream_t s
         g.X = sb.h;
         if (D.bf16) {
             g.norm_ss = sb.ssq;
-            g.norm_nb = sb.nsq;
+            g.norm_nb = nnb;
         }
     };
     // x += partial sums; then h = x * gamma plus the block sums of squares
     // (bf16) or h = RMSNorm(x) * gamma (fp32)
+    // (S < 0: the product has done it, with a sum of squares per -S columns)
     auto residual = [&](int S, const void* gamma) {
+        nnb = S < 0 ? D.d / -S : sb.nsq;
+        if (S < 0) return;
         if (D.bf16)
             launch_resid_reduce(D, T, sb.gpart, S, sb.x, gamma, sb.h, sb.ssq, sb.nsq, st);
         else
@@ -478,7 +483,7 @@ sd_status enqueue_forward(sd_ctx* c, Slot& s, const BatchView& bv, hipStream_t s
             g.epi = EPI_STORE;
             g.raw = 1;
             const int S = launch_gemm(D, g, sb, st);
-            launch_qkv_finish(D, bv, sb, c->kv, l, sb.gpart, S, w.qnorm, w.knorm, st);
+            launch_qkv_finish(D, bv, sb, c->kv, l, sb.gpart, S, nnb, w.qnorm, w.knorm, st);
         }
         {
             ProfScope ps(c, SD_K_ATTN, st);
@@ -497,6 +502,7 @@ sd_status enqueue_forward(sd_ctx* c, Slot& s, const BatchView& bv, hipStream_t s
             o.T = T;
             o.epi = EPI_STORE;
             o.raw = 1;
+            o.res_gamma = w.norm2;
             const int S = launch_gemm(D, o, sb, st);
             residual(S, w.norm2);
         }
@@ -533,8 +539,9 @@ sd_status enqueue_forward(sd_ctx* c, Slot& s, const BatchView& bv, hipStream_t s
             dn.T = T;
             dn.epi = EPI_STORE;
             dn.raw = 1;
-            const int S = launch_gemm(D, dn, sb, st);
             const void* gnext = l + 1 < D.L ? c->layers[l + 1].norm1 : c->w.norm_f;
+            dn.res_gamma = gnext;
+            const int S = launch_gemm(D, dn, sb, st);
             residual(S, gnext);
         }
     }

@@ -66,6 +66,35 @@ __device__ __forceinline__ float wave_sum(float v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
+// Up to 512 block sums of row t of [rows][n] (n > 8: a multiple of 4), lanes
+// over the blocks, four a load: request them (no branches, so that loads that
+// follow are not held back), then add them up.  Rows past the end give 0.  The
+// last row's load may touch 12 bytes past the array (the caller's buffer is
+// followed by others); those elements are not added.
+__device__ __forceinline__ void row_blocks_load(const float* v, int rows, int n, int t, int lane, f32x4 (&q)[2]) {
+    const __amdgpu_buffer_rsrc_t r =
+        __builtin_amdgcn_make_buffer_rsrc((void*)v, (short)0, (rows * n + 4) * 4, 0x00020000);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const int i = 4 * lane + 256 * b;
+        q[b] = __builtin_bit_cast(
+            f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, t < rows && i < n ? (t * n + i) * 4 : (int)0x80000000u, 0, 0));
+    }
+}
+__device__ __forceinline__ float row_blocks_sum(const f32x4 (&q)[2], int n, int lane) {
+    float s = 0.f;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s += 4 * lane + 256 * b + e < n ? q[b][e] : 0.f;
+    return wave_sum(s);
+}
+// sum of n block sums by one wave: lanes over the blocks, then the lanes
+__device__ __forceinline__ float lane_blocks_sum(const float* v, int n, int lane) {
+    float s = 0.f;
+    for (int b = lane; b < n; b += 64) s += v[b];
+    return wave_sum(s);
+}
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));

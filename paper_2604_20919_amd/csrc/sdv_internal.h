@@ -81,7 +81,8 @@ struct SlotBufs {
     int32_t* tok;     // [Tmax]
     float* cs;        // [Tmax][hd/2][2]
     float* x;         // [Tmax][d]
-    float* ssq;       // [Tmax][nsq] sums of squares of x per 1024-column block
+    float* ssq;       // [Tmax][nsq] sums of squares of x per 1024-column block, or
+                      // [T][<= kFewBlocks] per few columns after a few-slot product
                       // (bf16 configuration: h holds x * gamma and the
                       // consumers of RMSNorm(x) scale their outputs by rstd)
     int nsq;
@@ -150,14 +151,20 @@ struct GemmCall {
     int* sk_cnt;
     int32_t* flags;
     int sk_polls;
+    // raw products whose consumer is the residual add: the gain of the norm
+    // that follows.  Few-slot products then run that step themselves (x, h
+    // and one sum of squares per c columns, norm_nb = N / c) and return -c
+    const void* res_gamma;
 };
 constexpr int kSkCounters = 4096;
+constexpr int kFewBlocks = 512;  // most block sums of squares per row a few-slot product writes
 // polls of a stream-K wait before it gives up (a fraction of a second)
 constexpr int kSkPollsDefault = 1 << 18;
 // Upper bound of the statistic groups of an lm_head of V rows (workgroups
 // of at least 128 rows, one more for rounding)
 inline int lm_stat_groups_max(int V) { return (V + 127) / 128 + 1; }
-// Returns the number of partial planes S (raw mode), else the splits used.
+// Returns the number of partial planes S (raw mode; negative: the residual
+// step is done, see res_gamma), else the splits used.
 int launch_gemm(const Dims& D, const GemmCall& g, const SlotBufs& sb, hipStream_t s);
 // bf16 configuration: x[t] += sum_s part[s][t] (split order), h = x * gamma
 // (activation planes) and the block sums of squares of the new x; the
@@ -174,7 +181,7 @@ void launch_embed_norm(const Dims& D, const BatchView& bv, const void* embed, co
 // QKV partial reduction fused with QK-norm, RoPE, query store and KV append
 // (bf16: the summed partials are first scaled by the slot's rstd)
 void launch_qkv_finish(const Dims& D, const BatchView& bv, const SlotBufs& sb, const KVPool& kv,
-                       int layer, const float* part, int S, const void* qn, const void* kn,
+                       int layer, const float* part, int S, int nnb, const void* qn, const void* kn,
                        hipStream_t s);
 size_t gemm_partial_floats(const Dims& D, int Tmax);
 void launch_pack(const void* s0, const void* s1, const void* s2, int seg1, int seg2, int mode,
