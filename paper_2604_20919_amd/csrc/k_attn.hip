@@ -44,6 +44,7 @@ struct AttnP {
     float scale_log2;  // log2(e) / sqrt(hd)
     float* apart;      // [items][rows_max][hd]
     float* aml;        // [items][rows_max][2]
+    bf16_t* out;       // [2][T][hq][hd]: items that are a user's whole context
 };
 
 constexpr int HD = 128;
@@ -116,6 +117,73 @@ __device__ __forceinline__ void lds_read8(bf16x8 (&f)[8], uint32_t a) {
         : "memory");
 }
 
+// One 32-token block (its K and V^T fragments) for one row tile.  Scores stay
+// in the raw (unscaled) domain until the exponent, which folds the scale in:
+// p = 2^(s*c - m*c) with c = log2(e)/sqrt(hd).  Blocks that every row sees
+// completely skip the causal/chunk mask; the running output is rescaled only
+// when some row's maximum grew; the row sum stays per lane until the end of
+// the chunk.  wait_v: called before the first use of the V^T fragments.
+template <class F>
+__device__ __forceinline__ void attn_block(const bf16x8 (&kfr)[8], const bf16x8 (&vfr)[8], const bf16x8 (&qf)[4],
+                                           const bf16x8 (&ql)[4], float& m, float& l, f32x4 (&o)[8], int lim,
+                                           int t0, int c1, int lg, bool full, float scale_log2, F wait_v) {
+    // S^T = K (Q_hi + Q_lo)^T
+    f32x4 sa = f32x4{0.f, 0.f, 0.f, 0.f}, sb = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ds = 0; ds < 4; ++ds) {
+        const bf16x8 ka = kfr[ds];
+        const bf16x8 kk = kfr[4 + ds];
+        sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qf[ds], sa, 0, 0, 0);
+        sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, ql[ds], sa, 0, 0, 0);
+        sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk, qf[ds], sb, 0, 0, 0);
+        sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk, ql[ds], sb, 0, 0, 0);
+    }
+    // lane holds the scores of its query row at tokens t0 + 8*lg + e
+    float sc[8];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        sc[e] = sa[e];
+        sc[4 + e] = sb[e];
+    }
+    if (!full) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int tok = t0 + 8 * lg + e;
+            sc[e] = (tok < c1 && tok <= lim) ? sc[e] : -INFINITY;
+        }
+    }
+    float bm = fmaxf(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])),
+                     fmaxf(fmaxf(sc[4], sc[5]), fmaxf(sc[6], sc[7])));
+    bm = row_max4(bm);
+    const float mn = fmaxf(m, bm);
+    const bool live = mn != -INFINITY;  // something visible for this row
+    const float ms = live ? mn * scale_log2 : 0.f;
+    const float alpha = live ? __builtin_amdgcn_exp2f((m - mn) * scale_log2) : 1.f;
+    // P as hi + lo bf16 pair (about 16 significant bits)
+    float rs = 0.f;
+    bf16x8 pb, pl;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const float pe = __builtin_amdgcn_exp2f(fmaf(sc[e], scale_log2, -ms));
+        rs += pe;
+        pb[e] = (__bf16)pe;
+        pl[e] = (__bf16)(pe - (float)pb[e]);
+    }
+    l = fmaf(l, alpha, rs);
+    m = mn;
+    if (__builtin_amdgcn_ballot_w64(alpha != 1.f)) {
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) o[dt] *= alpha;
+    }
+    wait_v();
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) {
+        const bf16x8 vf = vfr[dt];
+        o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pb, o[dt], 0, 0, 0);
+        o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pl, o[dt], 0, 0, 0);
+    }
+}
+
 // Per-item constants of the ring and the per-pass state of a wave's row tiles.
 struct AttnItem {
     int c0, c1, nblk, prefix, wave, lane, lg, g;
@@ -175,12 +243,7 @@ __device__ __forceinline__ void attn_ring(const AttnP& p, const AttnItem& ac, At
         __builtin_amdgcn_raw_ptr_buffer_load_lds(kres, (lds_void*)(dst + 768), 16, (int)((vpg1 ? pb1 : pb0) + gv + voff1), 0, 0, 0);
     };
 
-        // One 32-token block for this wave's row tiles.  Scores stay in the
-    // raw (unscaled) domain until the exponent, which folds the scale in:
-    // p = 2^(s*c - m*c) with c = log2(e)/sqrt(hd).  Blocks that every
-    // row sees completely skip the causal/chunk mask; the running output
-    // is rescaled only when some row's maximum grew; the row sum stays
-    // per lane until the end of the chunk.
+    // One 32-token block for this wave's row tiles.
     auto compute = [&](const uint4* buf, int blk) __attribute__((always_inline)) {
         const int t0 = c0 + blk * 32;
         const bool full = t0 + 32 <= c1 && t0 + 31 <= prefix;
@@ -201,64 +264,12 @@ __device__ __forceinline__ void attn_ring(const AttnP& p, const AttnItem& ac, At
 #pragma unroll
         for (int i = 0; i < RT_MAX; ++i) {
             if (!act[i]) continue;
-            // S^T = K (Q_hi + Q_lo)^T
-            f32x4 sa = f32x4{0.f, 0.f, 0.f, 0.f}, sb = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ds = 0; ds < 4; ++ds) {
-                const bf16x8 ka = kfr[ds];
-                const bf16x8 kk = kfr[4 + ds];
-                sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qf[i][ds], sa, 0, 0, 0);
-                sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, ql[i][ds], sa, 0, 0, 0);
-                sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk, qf[i][ds], sb, 0, 0, 0);
-                sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk, ql[i][ds], sb, 0, 0, 0);
-            }
-            // lane holds the scores of its query row at tokens t0 + 8*lg + e
-            float sc[8];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                sc[e] = sa[e];
-                sc[4 + e] = sb[e];
-            }
-            if (!full) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int tok = t0 + 8 * lg + e;
-                    sc[e] = (tok < c1 && tok <= lim[i]) ? sc[e] : -INFINITY;
-                }
-            }
-            float bm = fmaxf(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])),
-                             fmaxf(fmaxf(sc[4], sc[5]), fmaxf(sc[6], sc[7])));
-            bm = row_max4(bm);
-            const float mn = fmaxf(m[i], bm);
-            const bool live = mn != -INFINITY;  // something visible for this row
-            const float ms = live ? mn * p.scale_log2 : 0.f;
-            const float alpha = live ? __builtin_amdgcn_exp2f((m[i] - mn) * p.scale_log2) : 1.f;
-            // P as hi + lo bf16 pair (about 16 significant bits)
-            float rs = 0.f;
-            bf16x8 pb, pl;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float pe = __builtin_amdgcn_exp2f(fmaf(sc[e], p.scale_log2, -ms));
-                rs += pe;
-                pb[e] = (__bf16)pe;
-                pl[e] = (__bf16)(pe - (float)pb[e]);
-            }
-            l[i] = fmaf(l[i], alpha, rs);
-            m[i] = mn;
-            if (__builtin_amdgcn_ballot_w64(alpha != 1.f)) {
-#pragma unroll
-                for (int dt = 0; dt < 8; ++dt) o[i][dt] *= alpha;
-            }
-            if (i == 0)
-                asm volatile("s_waitcnt lgkmcnt(0)"
-                             : "+v"(vfr[0]), "+v"(vfr[1]), "+v"(vfr[2]), "+v"(vfr[3]), "+v"(vfr[4]),
-                               "+v"(vfr[5]), "+v"(vfr[6]), "+v"(vfr[7]));
-#pragma unroll
-            for (int dt = 0; dt < 8; ++dt) {
-                const bf16x8 vf = vfr[dt];
-                o[i][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pb, o[i][dt], 0, 0, 0);
-                o[i][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pl, o[i][dt], 0, 0, 0);
-            }
+            attn_block(kfr, vfr, qf[i], ql[i], m[i], l[i], o[i], lim[i], t0, c1, lg, full, p.scale_log2, [&]() {
+                if (i == 0)
+                    asm volatile("s_waitcnt lgkmcnt(0)"
+                                 : "+v"(vfr[0]), "+v"(vfr[1]), "+v"(vfr[2]), "+v"(vfr[3]), "+v"(vfr[4]),
+                                   "+v"(vfr[5]), "+v"(vfr[6]), "+v"(vfr[7]));
+            });
         }
     };
 
@@ -299,8 +310,119 @@ __device__ __forceinline__ void attn_ring(const AttnP& p, const AttnItem& ac, At
 
 }
 
+// Short items of at most two row tiles (attn_item_few: drafting steps, small
+// models, short drafts).  They are bound by memory latency, not by bytes: in
+// the ring a block is requested when its predecessor's predecessor is done, and
+// only as many waves as there are row tiles multiply.  Here the waves share out
+// the blocks (one tile: four stripes; two tiles: two stripes, two waves each),
+// at most two each, requested at once straight into registers, and merge the
+// stripes through LDS.  An item that is a user's whole context writes the
+// attention output itself.  bv.few: the host's choice for the batch (every
+// context at most five blocks, or at most one item per CU and contexts past 512
+// tokens); elsewhere the ring is as fast or faster (a Qwen3-1.7B step of 14
+// users of 1000 tokens, 224 an item: 2008 us here, 1972 in the ring).  One user
+// of 2000 tokens 1635 -> 1456 us a step, of 1500 1557 -> 1449; 8 users of 134
+// tokens, 48 slots, 2052 -> 2005.
+__device__ __forceinline__ void attn_few(const AttnP& p, const AttnItem& ac, int item, int b, int R, int tbase,
+                                         int ntiles, uint4* r0, uint4* r1, float2 (*ml)[16]) {
+    const int wave = ac.wave, lane = ac.lane, lg = ac.lg, lr = lane & 15, g = ac.g;
+    const int c0 = ac.c0, c1 = ac.c1, nblk = ac.nblk, prefix = ac.prefix, G = p.G;
+    const cint32_t* pt = ac.pt;
+    const int wv = __builtin_amdgcn_readfirstlane(wave);
+    const int ns = ntiles == 1 ? 4 : 2;  // stripes
+    const int tile = ntiles == 1 ? 0 : wv & 1, stripe = ntiles == 1 ? wv : wv >> 1;
+    const uint32_t page_bytes = (uint32_t)(p.kv.page_elems() * 2);
+    const uint32_t gk = (uint32_t)(p.kv.k_off(0, 0, g) * 2), gv = (uint32_t)(p.kv.v_off(0, 0, g) * 2);
+    const __amdgpu_buffer_rsrc_t kres = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)((const char*)p.kv.base + p.kv.k_off(p.layer, 0, 0) * 2), (short)0,
+        (int)(uint32_t)((uint64_t)p.kv.n_pages * page_bytes), 0x00020000);
+    // lane sources, as k_slot_src / v_slot_src give them: K rows of the two
+    // token halves, V^T
+    const int kt0 = 8 * (lr >> 2) + (lr & 3), kt1 = kt0 + 4;
+    const uint32_t ko0 = gk + (uint32_t)(((kt0 & 15) * HD + 8 * lg) * 2);
+    const uint32_t ko1 = gk + (uint32_t)(((kt1 & 15) * HD + 8 * lg) * 2);
+    const uint32_t vo = gv + (uint32_t)((lr * kPageTokens + 8 * (lg & 1)) * 2);
+    auto load = [&](bf16x8 (&kf)[8], bf16x8 (&vf)[8], int blk) __attribute__((always_inline)) {
+        // tokens past the chunk end: the chunk's last page (masked, V finite)
+        const int t0 = c0 + blk * 32;
+        const uint32_t pb0 = (uint32_t)pt[min(t0, c1 - 1) >> 4] * page_bytes;
+        const uint32_t pb1 = (uint32_t)pt[min(t0 + 16, c1 - 1) >> 4] * page_bytes;
+        const uint32_t a0 = ko0 + (kt0 >> 4 ? pb1 : pb0), a1 = ko1 + (kt1 >> 4 ? pb1 : pb0);
+        const uint32_t av = vo + (lg >> 1 ? pb1 : pb0);
+#pragma unroll
+        for (int ds = 0; ds < 4; ++ds) {
+            kf[ds] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(kres, (int)a0 + 64 * ds, 0, 0));
+            kf[4 + ds] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(kres, (int)a1 + 64 * ds, 0, 0));
+        }
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt)
+            vf[dt] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(kres, (int)av + 512 * dt, 0, 0));
+    };
+    const int row = tile * 16 + lr;
+    const bool ok = row < R;
+    const int j = ok ? row / G : 0, hh = ok ? row % G : 0;
+    const bf16_t* qs = p.q + ((size_t)(tbase + j) * p.hq + g * G + hh) * HD + 8 * lg;
+    const size_t qpl = (size_t)p.bv.T * p.hq * HD;
+    bf16x8 qf[4], ql[4], ka[8], va[8], kb[8], vb[8];
+#pragma unroll
+    for (int ds = 0; ds < 4; ++ds) {
+        qf[ds] = *(const bf16x8*)(qs + ds * 32);  // rows past R: the first row's (their outputs are not stored)
+        ql[ds] = *(const bf16x8*)(qs + qpl + ds * 32);
+    }
+    if (stripe < nblk) load(ka, va, stripe);
+    if (stripe + ns < nblk) load(kb, vb, stripe + ns);
+    __builtin_amdgcn_sched_barrier(0);
+    const int lim = prefix + j;
+    float m = -INFINITY, l = 0.f;
+    f32x4 o[8];
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto block = [&](const bf16x8 (&kf)[8], const bf16x8 (&vf)[8], int k) __attribute__((always_inline)) {
+        const int t0 = c0 + k * 32;
+        attn_block(kf, vf, qf, ql, m, l, o, lim, t0, c1, lg, t0 + 32 <= c1 && t0 + 31 <= prefix, p.scale_log2, [] {});
+    };
+    if (stripe < nblk) block(ka, va, stripe);
+    if (stripe + ns < nblk) block(kb, vb, stripe + ns);
+    const float lsum = row_sum4(l);
+    f32x4* os = (f32x4*)((wave < 2 ? r0 : r1) + (wave & 1) * 512);
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) os[dt * 64 + lane] = o[dt];
+    if (lg == 0) ml[wave][lr] = float2{m == -INFINITY ? -INFINITY : m * p.scale_log2, lsum};
+    __syncthreads();
+    const int i0 = p.bv.item_off[b];
+    const bool solo = p.bv.item_off[b + 1] - i0 == p.hkv;
+    // piece (tile, dt, lane) of 16 bytes: row lane % 16, dims 16 * dt + 4 * (lane / 16) ..
+    for (int e = threadIdx.x; e < ntiles * 512; e += 256) {
+        const int tl = e >> 9, dt = (e >> 6) & 7, ln = e & 63, rr = ln & 15, orow = tl * 16 + rr;
+        if (orow >= R) continue;
+        float M = -INFINITY;
+        for (int s = 0; s < ns; ++s) M = fmaxf(M, ml[ntiles == 1 ? s : 2 * s + tl][rr].x);
+        f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f};
+        float L = 0.f;
+        for (int s = 0; s < ns; ++s) {  // stripe order
+            const int w = ntiles == 1 ? s : 2 * s + tl;
+            const float2 v = ml[w][rr];
+            const float f = v.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(v.x - M);
+            L += v.y * f;
+            a += ((const f32x4*)((w < 2 ? r0 : r1) + (w & 1) * 512))[dt * 64 + ln] * f;
+        }
+        const int d0 = dt * 16 + 4 * (ln >> 4);
+        if (solo) {
+            const float inv = 1.0f / L;
+            const float ov[4] = {a[0] * inv, a[1] * inv, a[2] * inv, a[3] * inv};
+            const int jj = orow / G;
+            st_act4(p.out, qpl, ((size_t)(tbase + jj) * p.hq + g * G + orow % G) * HD + d0, ov);
+        } else {
+            const size_t pr = (size_t)item * p.bv.rows_max + orow;
+            *(f32x4*)(p.apart + pr * HD + d0) = a;
+            if (d0 == 0) *(float2*)(p.aml + pr * 2) = float2{M, L};
+        }
+    }
+}
+
 template <int NBUF>
-__device__ __forceinline__ void attn_bf16_body(const AttnP& p, uint4* r0, uint4* r1, uint4* r2, uint4* r3) {
+__device__ __forceinline__ void attn_bf16_body(const AttnP& p, uint4* r0, uint4* r1, uint4* r2, uint4* r3,
+                                               float2 (*ml)[16]) {
     // The batch metadata is read-only while the kernel runs: reading it
     // through the constant address space gives scalar loads, which keep the
     // vector memory counter (waited on below) free of anything but KV.
@@ -336,6 +458,10 @@ __device__ __forceinline__ void attn_bf16_body(const AttnP& p, uint4* r0, uint4*
     ac.kpg0 = kpg0; ac.koff0 = koff0; ac.kpg1 = kpg1; ac.koff1 = koff1;
     ac.vpg0 = vpg0; ac.voff0 = voff0; ac.vpg1 = vpg1; ac.voff1 = voff1;
     const int ntiles = (R + 15) >> 4;
+    if (p.bv.few && attn_item_few(R, nblk)) {
+        attn_few(p, ac, item, b, R, tbase, ntiles, r0, r1, ml);
+        return;
+    }
     for (int rp = 0; rp < ntiles; rp += 4 * RT_MAX) {
         // this wave's row tiles in this pass: rp + wave + 4*i
         AttnState st;
@@ -397,7 +523,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __shared__ __attribute__((aligned(16))) uint4 kv1[1024];
     __shared__ __attribute__((aligned(16))) uint4 kv2[NBUF > 2 ? 1024 : 1];
     __shared__ __attribute__((aligned(16))) uint4 kv3[NBUF > 3 ? 1024 : 1];
-    attn_bf16_body<NBUF>(p, kv0, kv1, kv2, kv3);
+    __shared__ float2 ml[4][16];
+    attn_bf16_body<NBUF>(p, kv0, kv1, kv2, kv3, ml);
 }
 
 // Merge the partials of the chunks of (b, g) for one query row in chunk
@@ -416,6 +543,8 @@ __global__ __launch_bounds__(256) void k_attn_combine(BatchView bv, const float*
     const int b = bv.slot_b[t], j = bv.slot_j[t];
     const int row = j * G + hh;
     const int i0 = bv.item_off[b], nch = (bv.item_off[b + 1] - i0) / hkv;
+    // a short context in one item: the item wrote the output
+    if (nch == 1 && bv.few && attn_item_few((bv.L[b] + 1) * G, (bv.prefix[b] + bv.L[b] + 32) >> 5)) return;
     const int p0 = i0 + g * nch, p1 = p0 + nch;
     float M = -INFINITY, Ls = 0.f;
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -557,8 +686,10 @@ void launch_attention(const Dims& D, const BatchView& bv, const SlotBufs& sb, co
     p.scale_log2 = 1.4426950408889634f / sqrtf((float)D.hd);
     p.apart = sb.apart;
     p.aml = sb.aml;
+    p.out = (bf16_t*)sb.attn;
     hipLaunchKernelGGL(k_attn_bf16<kAttnBuffers>, dim3(bv.n_items), dim3(256), 0, s, p);
     // half a wave per (slot, query head)
+    if (!bv.combine) return;
     hipLaunchKernelGGL(k_attn_combine, dim3((bv.T * D.hq + 7) / 8), dim3(256), 0, s, bv, sb.apart,
                        sb.aml, (bf16_t*)sb.attn, D.hq, D.hkv);
 }

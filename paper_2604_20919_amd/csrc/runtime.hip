@@ -316,7 +316,8 @@ sd_status collect_batch(sd_ctx* c, int32_t batch, int32_t n_users, const int32_t
 }
 
 // Write the staging block for the batch into the slot's pinned buffer.
-void build_stage(sd_ctx* c, Slot& s, int mode, bool with_items, int* n_items, int* rows_max) {
+void build_stage(sd_ctx* c, Slot& s, int mode, bool with_items, int* n_items, int* rows_max,
+                 int* combine, int* few) {
     const Layout& L = c->lay;
     char* st = s.stage_host;
     int32_t* user = (int32_t*)(st + L.st_user);
@@ -353,12 +354,33 @@ void build_stage(sd_ctx* c, Slot& s, int mode, bool with_items, int* n_items, in
     // stream of a one-tile layer at 80 slots), so its chunks are shortened
     // in proportion and the items end together.
     const int G = c->D.G();
+    auto rows = [&](int b) { return (s.L[b] + 1) * G; };
+    auto context = [&](int b) { return c->users[s.users[b]].prefix + s.L[b] + 1; };
+    // Batches whose every context is one short item per (user, KV head): the
+    // items write the attention output, there are no partials to merge (up to
+    // five blocks: 8 users of 134 tokens 2052 -> 2005 us a Qwen3-1.7B pass; one
+    // user of 200 tokens, seven blocks, 1364 -> 1381)
+    bool solo = true;
+    for (int b = 0; b < s.B; ++b) {
+        const int blocks = ceil_div(context(b), 32);
+        solo &= blocks <= 5 && attn_item_few(rows(b), blocks);
+    }
+    *combine = !solo;
     auto weight = [&](int b) {  // cost per token in tenths
         const int tiles = ceil_div((s.L[b] + 1) * G, 16);
         return 10 + 3 * (ceil_div(tiles, 4) - 1);
     };
+    // With few rows four waves share out an item's blocks, in little more time
+    // than one block takes: where that leaves at most one item per CU, contexts
+    // that would else be more than 16 chunks get longer items, so that the
+    // merge, which takes eight at a time, is done in one go (below, the two
+    // cost the same: one user of 300 or 400 tokens 1386 -> 1421, 1395 -> 1417)
+    bool longer = false;
+    for (int b = 0; b < s.B; ++b) longer |= attn_item_few(rows(b), 1) && context(b) > 512;
     auto user_chunk = [&](int b, int ch) {  // chunk length of user b for base length ch
-        return std::max(32, (int)((long)ch * 10 / weight(b)) & ~31);
+        const int most = attn_item_few(rows(b), 8) ? 256 : attn_item_few(rows(b), 4) ? 128 : 32;
+        const int lo = longer && context(b) > 512 ? std::min(most, (ceil_div(context(b), 8) + 31) & ~31) : 32;
+        return std::max(std::max(lo, 32), (int)((long)ch * 10 / weight(b)) & ~31);
     };
     auto n_items_for = [&](int ch) {
         long n = 0;
@@ -368,8 +390,18 @@ void build_stage(sd_ctx* c, Slot& s, int mode, bool with_items, int* n_items, in
     };
     // (ends: once every user's chunk holds its whole context there are
     // B * hkv <= cap items)
-    int chunk = (int)std::max<long>(32, ((total * hkv + cap - 1) / cap + 31) & ~31L);
-    while (n_items_for(chunk) > cap) chunk += 32;
+    auto base_chunk = [&]() {
+        int ch = (int)std::max<long>(32, ((total * hkv + cap - 1) / cap + 31) & ~31L);
+        while (n_items_for(ch) > cap) ch += 32;
+        return ch;
+    };
+    int chunk = base_chunk();
+    *few = solo || (longer && n_items_for(chunk) <= c->attn_cap / kAttnWGsPerCU);
+    if (longer && !*few) {
+        longer = false;
+        chunk = base_chunk();
+    }
+    if (solo) chunk = 256;
     for (int b = 0; b < s.B; ++b) {
         const User& u = c->users[s.users[b]];
         user[b] = s.users[b];
@@ -911,7 +943,7 @@ static sd_status enqueue_pass(sd_ctx* c, Slot& s, const BatchView& bv, const flo
 static std::vector<int64_t> launch_key(sd_ctx* c, const Slot& s, const BatchView& bv,
                                        hipStream_t st) {
     std::vector<int64_t> k = {bv.B, bv.T, bv.nd, bv.mode, (int64_t)bv.seed, (int64_t)bv.round,
-                              bv.n_items, bv.rows_max, (int64_t)(intptr_t)bv.drafts,
+                              bv.n_items, bv.rows_max, bv.combine, bv.few, (int64_t)(intptr_t)bv.drafts,
                               (int64_t)(intptr_t)bv.q, (int64_t)(intptr_t)bv.accept_u,
                               (int64_t)(intptr_t)st, c->sk_polls};
     for (int b = 0; b < s.B; ++b) {
@@ -1016,8 +1048,8 @@ static sd_status submit(sd_ctx* c, int32_t batch, int32_t n_users, const int32_t
     s.batch = batch;
     s.sample_only = sample_only;
     s.logits_ok = sample_only || pass_writes_logits(c, mode, probs);
-    int n_items = 0, rows_max = 0;
-    build_stage(c, s, mode, !sample_only, &n_items, &rows_max);
+    int n_items = 0, rows_max = 0, combine = 0, few = 0;
+    build_stage(c, s, mode, !sample_only, &n_items, &rows_max, &combine, &few);
     BatchView bv = make_view(c, s);
     bv.B = s.B;
     bv.T = T;
@@ -1026,6 +1058,8 @@ static sd_status submit(sd_ctx* c, int32_t batch, int32_t n_users, const int32_t
     bv.seed = seed;
     bv.round = round;
     bv.n_items = n_items;
+    bv.combine = combine;
+    bv.few = few;
     bv.rows_max = rows_max;
     bv.drafts = draft_tokens;
     bv.q = q;

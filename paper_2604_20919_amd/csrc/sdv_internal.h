@@ -10,6 +10,11 @@ constexpr int kPageTokens = 16;   // tokens per KV page
 constexpr int kAttnItemsMax = 1024;  // attention work items per batch (beyond one per (user, KV head))
 constexpr int kAttnWGsPerCU = 2;     // co-resident attention workgroups per CU (register bound)
 constexpr int kAttnBuffers = 2;      // LDS ring of the attention kernel (buffers - 1 blocks in flight)
+// Attention items whose four waves share out the 32-token blocks, two a wave:
+// at most 16 query rows and 8 blocks, or 32 rows (two waves a block) and 4.
+__host__ __device__ inline bool attn_item_few(int rows, int blocks) {
+    return (rows <= 16 && blocks <= 8) || (rows <= 32 && blocks <= 4);
+}
 constexpr int kVocabChunks = 64;  // vocab split of the sampler kernels (at most 64: one wave merges)
 constexpr int kNormBlock = 1024;   // columns per sum-of-squares block of x
 constexpr int kNormKMax = 8192;    // widest model dimension the GEMM can normalise on load
@@ -50,6 +55,8 @@ struct BatchView {
     uint64_t seed, round;
     int max_pages;     // page-table row length
     int n_items;       // attention work items
+    int few;           // short items of few rows leave the ring (attn_item_few)
+    int combine;       // 0: every user's context is one item that writes the output itself
     int rows_max;      // (max l_m + 1) * G, rows of an attention partial
     const int32_t* user_id;    // [B] global user id
     const int32_t* prefix;     // [B] i_m
