@@ -363,7 +363,9 @@ sd_status sd_debug_logits(sd_ctx* ctx, int32_t batch, float* dst, sd_stream stre
  * sums; after max_polls polls it gives up, and sd_accept of that batch
  * returns SD_EDEVICE.  max_polls = 0 gives up at once (to test that error
  * path); a negative value restores the default (2^18 polls).  Passes whose
- * product takes no split are not affected. */
+ * product takes no split are not affected.  Passes of more than 256 slots
+ * never wait: there 0 makes every workgroup compute the row tiles that it
+ * shares with another by itself (same results). */
 sd_status sd_debug_wait_limit(sd_ctx* ctx, int32_t max_polls);
 
 /*

@@ -83,9 +83,18 @@ struct GemmP {
     // tiles of one group; with more than one group, `tiles` row tiles make
     // tiles * ng work tiles
     int ng;
+    // continued sums: the (row tile, split, chunk) triples of a group dealt out
+    // as above to sk_nwg workgroups a group; a work tile is shared by two of
+    // them at most, and the second continues the sums of the first from a slot
+    // of `part` that begins at float sk_off
+    size_t sk_off;
     int* sk_cnt;
     int32_t* flags;  // device error bits (bit 2: a stream-K wait gave up)
 };
+
+// Work distribution of a 32x32 product: one work tile per workgroup; stream-K
+// with a tile's pieces added up by its last; continued sums.
+enum { SK_NONE = 0, SK_WAIT = 1, SK_CONT = 2 };
 
 // stream-K: first pair of workgroup w's range, and the workgroup whose range
 // holds pair i
@@ -572,8 +581,18 @@ __device__ __forceinline__ void lds_wait_tiles(bf16x8 (&f)[N]) {
 // Slot groups (ng > 1): workgroups b and b + 8 (the same XCD, dispatched
 // together) compute the same weight rows for consecutive groups of MT tiles,
 // so the second finds the weights in its XCD's L2.
-// SKF: stream-K (unsplit products, see GemmP).
-template <int MT, int EPI, bool SPLIT, int NW, int CS, bool SKF = false>
+// SK: work distribution.  SK_WAIT, stream-K of an unsplit product (GemmP).
+// SK_CONT, for more work tiles than workgroups: each takes an equal run of
+// (work tile, chunk) pairs, so at most two share a tile.  It first computes
+// the head of its last tile and leaves the sums in memory, then its whole
+// tiles, then the tail of its first tile, whose head the workgroup before it
+// has left in the meantime: the accumulators start from those sums, and every
+// output is one chain of products in order of k, bit for bit that of one
+// workgroup per tile.  Nothing waits: both count themselves once, and a tail
+// that counts before its head (or whose sk_polls is zero) computes the whole
+// tile itself.  Qwen3-32B shapes at T = 359, us: gate/up 321 (adding up the
+// pieces of a tile instead: 372), QKV / O / down on average 114.
+template <int MT, int EPI, bool SPLIT, int NW, int CS, int SK = SK_NONE>
 __global__ __launch_bounds__(64 * NW)
 __attribute__((amdgpu_waves_per_eu(1, CS == 2 ? 2 : MT >= 5 ? 1 : MT >= 3 ? 2 : 4)))
 void k_gemm32(GemmP p) {
@@ -581,9 +600,11 @@ void k_gemm32(GemmP p) {
     constexpr int NS = 2;                // 32-row groups per wave
     constexpr int KC = 64;               // k per chunk
     static_assert(MT % CS == 0 && NW == 4 * CS, "whole tiles per wave, 256 weight rows per workgroup");
-    static_assert(!SKF || (!SPLIT && EPI == EPI_SWIGLU), "stream-K: the unsplit SwiGLU product");
+    static_assert(SK != SK_WAIT || (!SPLIT && EPI == EPI_SWIGLU), "stream-K: the unsplit SwiGLU product");
+    static_assert(SK != SK_CONT || SPLIT || EPI == EPI_SWIGLU, "continued sums: split products and SwiGLU");
     constexpr int MTW = MT / CS;         // slot tiles per wave
     constexpr int NTH = 64 * NW;         // threads per workgroup
+    constexpr int PER4 = NS * MTW * 4;   // 16-byte accumulator pieces per thread
     constexpr int KS = KC / 16;          // MFMA k-steps per chunk
     // weight register sets: two, except where the registers hold only one
     constexpr int WD = MT == 8 ? 1 : 2;
@@ -595,36 +616,42 @@ void k_gemm32(GemmP p) {
     static_assert(XS_ELEMS * 2 <= 160 * 1024, "staging exceeds LDS");
     __shared__ __attribute__((aligned(16))) bf16_t xs[XS_ELEMS];
     __shared__ float rsl[SPLIT ? 1 : MT * 32];  // per-slot RMSNorm factor
+    __shared__ int sk_seen;  // SK_CONT: count of the shared tile before this workgroup's
 
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int lc = lane & 31, lh = lane >> 5;
     // Work tile of this workgroup: (row tile, k split), for one slot group.
     int bid = blockIdx.x, grp = 0;
-    if (!SKF && p.ng > 1) {
+    if (SK != SK_WAIT && p.ng > 1) {
         grp = (bid >> 3) % p.ng;
         bid = (bid >> 3) / p.ng * 8 + (bid & 7);
-        if (bid >= p.tiles * p.S) return;  // the grid is rounded up to 8 workgroups per group
+        if (SK == SK_NONE && bid >= p.tiles * p.S) return;  // the grid is rounded up to 8 workgroups per group
     }
-    // Stream-K: the workgroup's range of (work tile, chunk) pairs is cut at
-    // the tile ends into pieces.  The piece of the last tile is taken first
-    // (when it does not end its tile, another workgroup waits for it), then
-    // the others in order.  Otherwise one piece: the whole k range of a split.
+    // Stream-K and continued sums: the workgroup's range of (work tile, chunk)
+    // pairs is cut at the tile ends into pieces.  The piece of the last tile is
+    // taken first (when it does not end its tile, another workgroup needs it).
+    // Stream-K then goes on in order, continued sums leave the first tile for
+    // the end.  Otherwise one piece: the whole k range of a split.
+    const int uch = SK == SK_CONT ? p.kchunks / p.S : p.kchunks;  // chunks per work tile
     int sk_np = 1, sk_wb = 0, sk_we = 0, sk_t0 = 0;
-    if constexpr (SKF) {
-        const int total = p.tiles * p.ng * p.kchunks;
-        sk_wb = sk_begin(blockIdx.x, total, p.sk_nwg);
-        sk_we = sk_begin(blockIdx.x + 1, total, p.sk_nwg);
-        sk_t0 = sk_wb / p.kchunks;
-        sk_np = (sk_we - 1) / p.kchunks - sk_t0 + 1;
+    if constexpr (SK != SK_NONE) {
+        const int total = p.tiles * (SPLIT ? p.S : 1) * uch;
+        sk_wb = sk_begin(bid, total, p.sk_nwg);
+        sk_we = sk_begin(bid + 1, total, p.sk_nwg);
+        sk_t0 = sk_wb / uch;
+        sk_np = (sk_we - 1) / uch - sk_t0 + 1;
     }
     for (int piece = 0; piece < sk_np; ++piece) {
     // the last piece's epilogue reads the row factors this one overwrites
-    if (SKF && piece > 0) __syncthreads();
-    const int split = SPLIT ? bid % p.S : 0;
-    // SKF: work tile (row tile, group), groups of a row tile consecutive
-    const int skt = SKF ? sk_t0 + (piece == 0 ? sk_np - 1 : piece - 1) : 0;
-    const int wgi = SKF ? skt / p.ng : (SPLIT ? bid / p.S : bid);
-    if constexpr (SKF) grp = skt % p.ng;
+    if (SK != SK_NONE && piece > 0) __syncthreads();
+    const int skt = SK == SK_NONE ? 0
+                    : sk_t0 + (piece == 0                             ? sk_np - 1
+                               : SK == SK_WAIT                        ? piece - 1
+                               : piece == sk_np - 1                   ? 0
+                                                                      : piece);
+    const int wt = SK == SK_NONE ? bid : skt;  // work tile (row tile, split)
+    const int split = SPLIT ? wt % p.S : 0;
+    const int wgi = SPLIT ? wt / p.S : wt;
     const int tb = grp * MT * 32;  // first slot of the group
 
     // Buffer resources: one uniform resource per operand, fixed 32-bit
@@ -659,9 +686,49 @@ void k_gemm32(GemmP p) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[s][m][e] = 0.f;
 
-    const int c_begin = SKF ? max(sk_wb - skt * p.kchunks, 0) : split * p.kchunks / p.S;
-    const int c_end = SKF ? min(sk_we - skt * p.kchunks, p.kchunks) : (split + 1) * p.kchunks / p.S;
-    const int c_last = c_end - 1;
+    // chunks of the work tile that this piece computes
+    const int c_split = split * p.kchunks / p.S;
+    int c_lo = SK == SK_NONE ? 0 : max(sk_wb - skt * uch, 0);
+    const int c_hi = SK == SK_NONE ? (split + 1) * p.kchunks / p.S - c_split : min(sk_we - skt * uch, uch);
+    // sums of a shared tile: element j of thread i at j * NTH + i (16-byte
+    // pieces, coalesced)
+    auto sk_slot = [&](size_t i) {
+        return __builtin_amdgcn_make_buffer_rsrc((void*)(p.part + p.sk_off + i * (size_t)(NTH * PER4 * 4)), (short)0,
+                                                 NTH * PER4 * 16, 0x00020000);
+    };
+    if constexpr (SK == SK_CONT) {
+        if (c_lo > 0) {
+            const int head = (bid - 1) * p.ng + grp;
+            if (threadIdx.x == 0) {
+                const int n = __hip_atomic_fetch_add(p.sk_cnt + head, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                // the head has counted: back to zero for the next launch
+                if (n == 1) __hip_atomic_store(p.sk_cnt + head, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                sk_seen = p.sk_polls > 0 ? n : 0;
+            }
+            __syncthreads();
+            if (__builtin_amdgcn_readfirstlane(sk_seen) == 1) {
+                const __amdgpu_buffer_rsrc_t r = sk_slot(head);
+#pragma unroll
+                for (int s = 0; s < NS; ++s)
+#pragma unroll
+                    for (int m = 0; m < MTW; ++m)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const f32x4 f = __builtin_bit_cast(
+                                f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                           r, (((s * MTW + m) * 4 + q) * NTH + (int)threadIdx.x) * 16, 0, 17));
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[s][m][4 * q + e] = f[e];
+                        }
+                // (here, so that no wait for them is left to the first products)
+                wait_vm<0>();
+                __builtin_amdgcn_sched_barrier(0);
+            } else {
+                c_lo = 0;
+            }
+        }
+    }
+    const int c_begin = c_split + c_lo, c_end = c_split + c_hi;
     // RMSNorm row factors of the tile's slots (epilogues that scale by
     // them): loads issued ahead of the pipeline prologue, the factors go to
     // LDS before the first barrier
@@ -680,7 +747,7 @@ void k_gemm32(GemmP p) {
     // tile-plane instead of two; the wave that holds it multiplies it in the
     // plane-0 phases only
     const int last_n = p.T - tb - (MT - 1) * 32;
-    const bool pkl = last_n > 0 && last_n <= 16;
+    const bool pkl = p.ng == 1 && last_n > 0 && last_n <= 16;
     const bool pkl_half = pkl && half == CS - 1;
 
     // Two X buffers in LDS, WD weight register sets.  Per chunk c: the direct
@@ -805,39 +872,43 @@ void k_gemm32(GemmP p) {
         }
     }
 
-    int sk_ord = 0;  // earlier pieces of this tile to add (the tile's last piece)
-    if constexpr (SKF) {
-        // Partial sums travel through memory at system scope (written
-        // through, read past the caches), ordered by the count: stores, wait
-        // for them, barrier, then the count; the reader polls the count
-        // before it loads.  Slot layout: element j of thread i at j * NTH + i
-        // (16-byte pieces, coalesced).
-        constexpr int PER4 = NS * MTW * 4;  // 16-byte accumulator pieces per thread
-        const int total = p.tiles * p.ng * p.kchunks;
+    int sk_ord = 0;  // SK_WAIT: earlier pieces of this tile to add (the tile's last piece)
+    // Partial sums travel through memory at system scope (written through,
+    // read past the caches), ordered by the count: stores, wait for them,
+    // barrier, then the count; the reader reads the count before it loads.
+    auto leave_sums = [&](size_t slot, int* cnt) {
+        const __amdgpu_buffer_rsrc_t r = sk_slot(slot);
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int m = 0; m < MTW; ++m)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int j = (s * MTW + m) * 4 + q;
+                    const f32x4 v = f32x4{acc[s][m][4 * q], acc[s][m][4 * q + 1], acc[s][m][4 * q + 2],
+                                          acc[s][m][4 * q + 3]};
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r,
+                                                           (j * NTH + (int)threadIdx.x) * 16, 0, 17);
+                }
+        wait_vm<0>();
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const int n = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            // the tail came first and does without: back to zero
+            if (SK == SK_CONT && n == 1) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    };
+    if constexpr (SK == SK_CONT) {
+        if (c_hi < uch) {
+            leave_sums(bid * p.ng + grp, p.sk_cnt + bid * p.ng + grp);
+            continue;
+        }
+    }
+    if constexpr (SK == SK_WAIT) {
+        const int total = p.tiles * p.kchunks;
         const int ord = (int)blockIdx.x - sk_owner(skt * p.kchunks, total, p.sk_nwg);
-        auto slot_rsrc = [&](int o) {
-            return __builtin_amdgcn_make_buffer_rsrc(
-                (void*)(p.part + ((size_t)skt * p.sk_maxp + o) * (size_t)(NTH * PER4 * 4)), (short)0,
-                NTH * PER4 * 16, 0x00020000);
-        };
         if (c_end < p.kchunks) {
-            const __amdgpu_buffer_rsrc_t r = slot_rsrc(ord);
-#pragma unroll
-            for (int s = 0; s < NS; ++s)
-#pragma unroll
-                for (int m = 0; m < MTW; ++m)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int j = (s * MTW + m) * 4 + q;
-                        const f32x4 v = f32x4{acc[s][m][4 * q], acc[s][m][4 * q + 1], acc[s][m][4 * q + 2],
-                                              acc[s][m][4 * q + 3]};
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r,
-                                                               (j * NTH + (int)threadIdx.x) * 16, 0, 17);
-                    }
-            wait_vm<0>();
-            __syncthreads();
-            if (threadIdx.x == 0)
-                __hip_atomic_fetch_add(p.sk_cnt + skt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            leave_sums((size_t)skt * p.sk_maxp + ord, p.sk_cnt + skt);
             continue;
         }
         if (ord > 0) {
@@ -948,16 +1019,14 @@ void k_gemm32(GemmP p) {
             }
             __syncthreads();
         }
-        return;
+        continue;
     }
 #pragma unroll
     for (int m = 0; m < MTW; ++m) {
-        if constexpr (SKF) {
+        if constexpr (SK == SK_WAIT) {
             // the earlier pieces' sums of this slot tile, in piece order
             for (int o = 0; o < sk_ord; ++o) {
-                const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-                    (void*)(p.part + ((size_t)skt * p.sk_maxp + o) * (size_t)(NTH * NS * MTW * 16)), (short)0,
-                    NTH * NS * MTW * 64, 0x00020000);
+                const __amdgpu_buffer_rsrc_t r = sk_slot((size_t)skt * p.sk_maxp + o);
                 u32x4 v[NS][4];
 #pragma unroll
                 for (int s = 0; s < NS; ++s)
@@ -1411,19 +1480,23 @@ static GemmFn pick16(bool split, int epi) {
 }
 
 template <int MT, int CS>
-static GemmFn pick32(bool split, int epi, bool skf) {
+static GemmFn pick32(bool split, int epi, int sk) {
+    if constexpr (MT >= 5)
+        if (sk == SK_CONT)
+            return split ? k_gemm32<MT, EPI_STORE, true, 4 * CS, CS, SK_CONT>
+                         : k_gemm32<MT, EPI_SWIGLU, false, 4 * CS, CS, SK_CONT>;
     if (split) return k_gemm32<MT, EPI_STORE, true, 4 * CS, CS>;
     switch (epi) {
         case EPI_SWIGLU:
             if constexpr (MT >= 5)
-                if (skf) return k_gemm32<MT, EPI_SWIGLU, false, 4 * CS, CS, true>;
+                if (sk == SK_WAIT) return k_gemm32<MT, EPI_SWIGLU, false, 4 * CS, CS, SK_WAIT>;
             return k_gemm32<MT, EPI_SWIGLU, false, 4 * CS, CS>;
         case EPI_LMSTAT: return k_gemm32<MT, EPI_LMSTAT, false, 4 * CS, CS>;
         default: return k_gemm32<MT, EPI_STORE, false, 4 * CS, CS>;
     }
 }
 
-static GemmFn pick(const GemmShape& sh, bool split, int epi, bool skf = false) {
+static GemmFn pick(const GemmShape& sh, bool split, int epi, int sk = SK_NONE) {
     if (sh.F == 16) {
         switch (sh.MT) {
             case 1: return pick16<1>(split, epi);
@@ -1435,13 +1508,13 @@ static GemmFn pick(const GemmShape& sh, bool split, int epi, bool skf = false) {
         }
     }
     switch (sh.MT) {
-        case 1: return pick32<1, 1>(split, epi, skf);
-        case 2: return pick32<2, 1>(split, epi, skf);
-        case 3: return pick32<3, 1>(split, epi, skf);
-        case 4: return pick32<4, 1>(split, epi, skf);
-        case 5: return pick32<5, 1>(split, epi, skf);
-        case 6: return pick32<6, 2>(split, epi, skf);
-        default: return pick32<8, 2>(split, epi, skf);
+        case 1: return pick32<1, 1>(split, epi, sk);
+        case 2: return pick32<2, 1>(split, epi, sk);
+        case 3: return pick32<3, 1>(split, epi, sk);
+        case 4: return pick32<4, 1>(split, epi, sk);
+        case 5: return pick32<5, 1>(split, epi, sk);
+        case 6: return pick32<6, 2>(split, epi, sk);
+        default: return pick32<8, 2>(split, epi, sk);
     }
 }
 
@@ -1605,6 +1678,15 @@ int launch_gemm(const Dims& D, const GemmCall& g, const SlotBufs& sb, hipStream_
     const int upw = sh.NW / sh.CS;  // row units per workgroup
     p.tiles = (units + upw - 1) / upw;
     int S = g.epi == EPI_LMSTAT ? 1 : choose_splits(p.tiles * sh.NG, p.kchunks, sh.FILL);
+    // Two slot groups over a long k: the splits of 128-row workgroups at 1.25 to
+    // 1.75 a CU (Qwen3-32B QKV / O / down: 5 / 8 / 10 where a grid within the
+    // CUs has 3 / 6 / 6).  The sums are then added in the same order as by the
+    // plain 128-row form, which close decisions depend on; and the workgroups
+    // continue each other's sums, so that the count need not fit the CUs.
+    if (sh.NG > 1 && g.epi != EPI_LMSTAT) {
+        const int s128 = choose_splits((vcols + 127) / 128, p.kchunks, false);
+        if (p.kchunks % s128 == 0 && p.kchunks / s128 >= 16) S = s128;
+    }
     // four-wave split-K tiles over a short k (the Qwen3-1.7B QKV and O
     // projections, k = 2048): half the splits, so each split keeps four
     // 64-k chunks and the consumer reads half the partial planes (one
@@ -1639,33 +1721,48 @@ int launch_gemm(const Dims& D, const GemmCall& g, const SlotBufs& sb, hipStream_
     // two batches on two streams down)
     p.sk_nwg = 0;
     p.sk_maxp = 0;
+    p.sk_off = 0;
     p.ng = sh.NG;
     p.sk_polls = g.sk_polls;
     p.sk_cnt = g.sk_cnt;
     p.flags = g.flags;
-    const int wtiles = p.tiles * p.ng;  // (row tile, slot group) work tiles
-    if (!g.raw && g.epi == EPI_SWIGLU && sh.F == 32 && sh.MT >= 5 && S == 1 && g.sk_cnt && g.flags &&
-        p.tiles < cu_count() && wtiles <= kSkCounters) {
-        const int total = wtiles * p.kchunks, nwg = std::min(cu_count(), total);
+    if (!g.raw && g.epi == EPI_SWIGLU && sh.F == 32 && sh.MT >= 5 && sh.NG == 1 && S == 1 && g.sk_cnt && g.flags &&
+        p.tiles < cu_count() && p.tiles <= kSkCounters) {
+        const int total = p.tiles * p.kchunks, nwg = std::min(cu_count(), total);
         int maxp = 0;  // most pieces of a tile before its last
-        for (int t = 0; t < wtiles; ++t)
+        for (int t = 0; t < p.tiles; ++t)
             maxp = std::max(maxp, sk_owner(t * p.kchunks + p.kchunks - 1, total, nwg) -
                                       sk_owner(t * p.kchunks, total, nwg));
         const size_t slot_floats = (size_t)256 * sh.MT * 32;  // 256 rows, MT tiles of 32 slots
-        if (maxp >= 1 && (size_t)wtiles * maxp * slot_floats <= sb.gpart_floats) {
+        if (maxp >= 1 && (size_t)p.tiles * maxp * slot_floats <= sb.gpart_floats) {
             p.sk_nwg = nwg;
             p.sk_maxp = maxp;
-            hipLaunchKernelGGL(pick(sh, false, g.epi, true), dim3(nwg), dim3(64 * sh.NW), 0, s, p);
+            hipLaunchKernelGGL(pick(sh, false, g.epi, SK_WAIT), dim3(nwg), dim3(64 * sh.NW), 0, s, p);
             return 1;
         }
     }
+    // Continued sums for two slot groups whose work tiles are more than the
+    // CUs and no whole multiple
+    int sk = SK_NONE;
+    const bool split = g.raw || S > 1;
+    const int per_group = cu_count() / (8 * p.ng) * 8;
+    if (p.ng > 1 && (split || g.epi == EPI_SWIGLU) && g.sk_cnt && p.kchunks % S == 0 && per_group > 0 &&
+        p.tiles * S > per_group && p.tiles * S % per_group != 0 && per_group * p.ng <= kSkCounters) {
+        const size_t planes = split ? (size_t)S * g.T * p.vcols : 0;
+        const size_t slot_floats = (size_t)256 * sh.MT * 32;
+        if (planes + (size_t)per_group * p.ng * slot_floats <= sb.gpart_floats) {
+            sk = SK_CONT;
+            p.sk_nwg = per_group;
+            p.sk_off = planes;
+        }
+    }
     // slot groups: whole runs of 8 work tiles (one per XCD) for every group
-    const int grid = p.ng == 1 ? p.tiles * S : (p.tiles * S + 7) / 8 * 8 * p.ng;
+    const int grid = sk == SK_CONT ? p.sk_nwg * p.ng : p.ng == 1 ? p.tiles * S : (p.tiles * S + 7) / 8 * 8 * p.ng;
     if (g.raw) {
         // S partial planes [S][T][N] for a fused consumer to reduce
-        hipLaunchKernelGGL(pick(sh, true, EPI_STORE), dim3(grid), dim3(64 * sh.NW), 0, s, p);
+        hipLaunchKernelGGL(pick(sh, true, EPI_STORE, sk), dim3(grid), dim3(64 * sh.NW), 0, s, p);
     } else if (S == 1) {
-        hipLaunchKernelGGL(pick(sh, false, g.epi), dim3(grid), dim3(64 * sh.NW), 0, s, p);
+        hipLaunchKernelGGL(pick(sh, false, g.epi, sk), dim3(grid), dim3(64 * sh.NW), 0, s, p);
     } else {
         // a split SwiGLU product on four-wave tiles: its last split adds the
         // others' sums (a slot of fp32 accumulators per split and tile) and runs
@@ -1678,7 +1775,7 @@ int launch_gemm(const Dims& D, const GemmCall& g, const SlotBufs& sb, hipStream_
             hipLaunchKernelGGL(la, dim3(p.tiles * S), dim3(64 * sh.NW), 0, s, p);
             return S;
         }
-        hipLaunchKernelGGL(pick(sh, true, g.epi), dim3(grid), dim3(64 * sh.NW), 0, s, p);
+        hipLaunchKernelGGL(pick(sh, true, g.epi, sk), dim3(grid), dim3(64 * sh.NW), 0, s, p);
         const int ncols = g.epi == EPI_SWIGLU ? p.vcols / 2 : p.vcols;
         const int n = g.T * (ncols / 4);
         hipLaunchKernelGGL(pick_reduce(g.epi), dim3((n + 255) / 256), dim3(256), 0, s, p);

@@ -514,6 +514,8 @@ sd_status enqueue_forward(sd_ctx* c, Slot& s, const BatchView& bv, hipStream_t s
             g.T = T;
             g.epi = EPI_STORE;
             g.raw = 1;
+            g.sk_cnt = sb.skcnt;
+            g.sk_polls = c->sk_polls;
             const int S = launch_gemm(D, g, sb, st);
             launch_qkv_finish(D, bv, sb, c->kv, l, sb.gpart, S, nnb, w.qnorm, w.knorm, st);
         }
@@ -534,6 +536,8 @@ sd_status enqueue_forward(sd_ctx* c, Slot& s, const BatchView& bv, hipStream_t s
             o.T = T;
             o.epi = EPI_STORE;
             o.raw = 1;
+            o.sk_cnt = sb.skcnt;
+            o.sk_polls = c->sk_polls;
             o.res_gamma = w.norm2;
             const int S = launch_gemm(D, o, sb, st);
             residual(S, w.norm2);
@@ -571,6 +575,8 @@ sd_status enqueue_forward(sd_ctx* c, Slot& s, const BatchView& bv, hipStream_t s
             dn.T = T;
             dn.epi = EPI_STORE;
             dn.raw = 1;
+            dn.sk_cnt = sb.skcnt;
+            dn.sk_polls = c->sk_polls;
             const void* gnext = l + 1 < D.L ? c->layers[l + 1].norm1 : c->w.norm_f;
             dn.res_gamma = gnext;
             const int S = launch_gemm(D, dn, sb, st);

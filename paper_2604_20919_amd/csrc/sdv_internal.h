@@ -152,9 +152,9 @@ struct GemmCall {
     float* zd;
     const int32_t* dnext;
     int* groups_out;
-    // stream-K of the gate/up product (see k_gemm.hip): per-tile piece
-    // counters (kSkCounters, zero between launches), the device error bits
-    // and the polls of a wait before it gives up
+    // products whose workgroups share row tiles (see k_gemm.hip): counters
+    // (kSkCounters, zero between launches); stream-K of the gate/up product:
+    // the device error bits and the polls of a wait before it gives up
     int* sk_cnt;
     int32_t* flags;
     int sk_polls;
