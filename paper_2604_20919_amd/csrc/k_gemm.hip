@@ -1488,7 +1488,7 @@ static GemmFn pick32(bool split, int epi, int sk) {
     if (split) return k_gemm32<MT, EPI_STORE, true, 4 * CS, CS>;
     switch (epi) {
         case EPI_SWIGLU:
-            if constexpr (MT >= 5)
+            if constexpr (MT == 8)
                 if (sk == SK_WAIT) return k_gemm32<MT, EPI_SWIGLU, false, 4 * CS, CS, SK_WAIT>;
             return k_gemm32<MT, EPI_SWIGLU, false, 4 * CS, CS>;
         case EPI_LMSTAT: return k_gemm32<MT, EPI_LMSTAT, false, 4 * CS, CS>;
@@ -1714,11 +1714,11 @@ int launch_gemm(const Dims& D, const GemmCall& g, const SlotBufs& sb, hipStream_
     p.dnext = g.dnext;
     if (g.groups_out) *g.groups_out = p.tiles;
     // Stream-K for an unsplit SwiGLU product of fewer row tiles than CUs (the
-    // Qwen3-32B gate/up: 200) above 128 slots: T = 160 175 us, T = 224 242
-    // against 275 unsplit.  Below, the weights' stream bounds the product and
-    // the idle CUs cost less than the partial sums (T = 60: 114 against 96 us;
-    // T = 128: 154 against 157, but then one batch holds every CU, which slows
-    // two batches on two streams down)
+    // Qwen3-32B gate/up: 200) at 225-256 slots, where the idle CUs cost most.
+    // Its last pieces wait for earlier workgroups, so it stays out where it
+    // gives little: 16 layers at T = 132 / 160 / 192 / 224 took 6545 / 6804 /
+    // 7527 / 9111 us with it, 6640 / 6841 / 7584 / 9260 take without (the
+    // weights' stream bounds the smaller ones).
     p.sk_nwg = 0;
     p.sk_maxp = 0;
     p.sk_off = 0;
@@ -1726,14 +1726,14 @@ int launch_gemm(const Dims& D, const GemmCall& g, const SlotBufs& sb, hipStream_
     p.sk_polls = g.sk_polls;
     p.sk_cnt = g.sk_cnt;
     p.flags = g.flags;
-    if (!g.raw && g.epi == EPI_SWIGLU && sh.F == 32 && sh.MT >= 5 && sh.NG == 1 && S == 1 && g.sk_cnt && g.flags &&
+    if (!g.raw && g.epi == EPI_SWIGLU && sh.F == 32 && sh.MT == 8 && sh.NG == 1 && g.T > 224 && S == 1 && g.sk_cnt && g.flags &&
         p.tiles < cu_count() && p.tiles <= kSkCounters) {
         const int total = p.tiles * p.kchunks, nwg = std::min(cu_count(), total);
         int maxp = 0;  // most pieces of a tile before its last
         for (int t = 0; t < p.tiles; ++t)
             maxp = std::max(maxp, sk_owner(t * p.kchunks + p.kchunks - 1, total, nwg) -
                                       sk_owner(t * p.kchunks, total, nwg));
-        const size_t slot_floats = (size_t)256 * sh.MT * 32;  // 256 rows, MT tiles of 32 slots
+        const size_t slot_floats = (size_t)256 * 8 * 32;  // 256 rows, eight tiles of 32 slots
         if (maxp >= 1 && (size_t)p.tiles * maxp * slot_floats <= sb.gpart_floats) {
             p.sk_nwg = nwg;
             p.sk_maxp = maxp;

@@ -1,6 +1,6 @@
-"""Products of more than 256 slots run in two slot groups whose workgroups
-share out the row tiles unevenly: a tile that two of them compute is one chain
-of sums in order of k, continued from memory, so that
+"""Products above 128 slots: no waits up to 224 slots, and two slot groups above
+256, whose workgroups share out the row tiles unevenly: a tile that two of them
+compute is one chain of sums in order of k, continued from memory, so that
 
   * a user's logits do not depend on which group, tile or packed remainder its
     slots fall into (two users of the same prefix, keys, values and tokens, the
@@ -79,6 +79,28 @@ def test_logits_do_not_depend_on_the_slot_group(monkeypatch, model, T):
         v.wait_limit(limit)
         _pass(v, w, 0, b, d)
         assert _same(_result(v, w, 0, b), ref), limit
+    v.close()
+
+
+@pytest.mark.parametrize("T", [144, 176, 208, 224])
+def test_no_waits_up_to_224_slots(T):
+    """A gate/up product of more than half and fewer than all CUs' row tiles is
+    not split there: the pass does not depend on the wait limit."""
+    L = [11] * (T // 12) + ([T % 12 - 1] if T % 12 else [])
+    w = wl.custom_workload("tiny-wide-ffn", [(29 * i) % 80 for i in range(len(L))], L, seed=37)
+    dw = DeviceWeights(w.model, w.seed)
+    v = make_verifier(w, dw)
+    load_synthetic_kv(v, w)
+    b = w.batch(0)
+    assert b.T == T
+    for i, u in enumerate(b.users):
+        v.reset_user(int(u), int(b.prefix_len[i]), int(b.root[i]))
+    d = torch.from_numpy(np.ascontiguousarray(b.drafts)).cuda()
+    _pass(v, w, 0, b, d)
+    ref = _result(v, w, 0, b)
+    v.wait_limit(0)
+    _pass(v, w, 0, b, d)
+    assert _same(_result(v, w, 0, b), ref)
     v.close()
 
 
