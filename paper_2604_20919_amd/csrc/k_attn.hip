@@ -627,7 +627,9 @@ __global__ __launch_bounds__(256) void k_attn_f32(BatchView bv, const float* q, 
         m = mn;
         a0 *= al;
         a1 *= al;
+        wave_lds_order();     // the previous block's weights have been read
         ps[wave][lane] = pe;  // read back by the same wave
+        wave_lds_order();
         const int nt = min(64, n - c0);
         for (int p0 = 0; p0 < nt; p0 += kPageTokens) {
             const float* vb = base + kv.v_off(layer, pt[(c0 + p0) >> 4], g);

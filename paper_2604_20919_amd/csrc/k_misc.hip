@@ -592,7 +592,7 @@ __global__ __launch_bounds__(256) void k_kv_copy_page(KVPool kv, KVCopyPages pag
             if (t >= lo && t < hi) *(uint4*)(kp + t * HD + c) = kr[i];
             *(uint4*)(sw + t * ROW + c) = vr[i];
         }
-        // (one wave: its LDS accesses are in order, the compiler waits for them)
+        wave_lds_order();
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int d = lane + 64 * i;
@@ -619,6 +619,7 @@ __global__ __launch_bounds__(256) void k_kv_copy_page(KVPool kv, KVCopyPages pag
 #pragma unroll
             for (int t = 0; t < kPageTokens; ++t) sw[t * ROW + d] = (bf16_t)(w[t >> 1] >> (16 * (t & 1)));
         }
+        wave_lds_order();
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int t = (lane >> 4) + 4 * i;

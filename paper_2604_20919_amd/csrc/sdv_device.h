@@ -158,6 +158,15 @@ __device__ __forceinline__ void barrier_nofence() {
     asm volatile("" ::: "memory");
 }
 
+// Orders LDS accesses between the lanes of one wave: what its lanes wrote before
+// is what they read after.  The hardware runs a wave's LDS accesses in order;
+// this keeps the compiler from reordering them (it emits at most a wait).
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---------------------------------------------------------------------------
 // Philox-4x64-10 (Salmon et al., SC'11).  Ten rounds of: multiply words 0 and
 // 2 by the round multipliers, swap halves, xor in the round key; the key
