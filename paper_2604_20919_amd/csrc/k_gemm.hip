@@ -820,11 +820,14 @@ void k_gemm32(GemmP p) {
             w[s] = __builtin_bit_cast(
                 bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wres, woff[s], (c * KS + ks) * 512, kWeightAux));
     };
+    // the wait below counts loads: only arithmetic may move across these barriers
     dma_x(c_begin, 0);
+    __builtin_amdgcn_sched_barrier(1);
 #pragma unroll
     for (int u = 0; u < WD; ++u)
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) load_w_ks(wr[u][ks], c_begin + u, ks);
+    __builtin_amdgcn_sched_barrier(1);
     if constexpr (!SPLIT) {
 #pragma unroll
         for (int i = 0; i < NSPT; ++i) {
