@@ -153,10 +153,22 @@ __device__ __forceinline__ float rstd_of(const GemmP& p, const float (&v)[kNormK
     for (int b = 0; b < kNormKMax / kNormBlock; ++b) ss += v[b];
     return 1.0f / sqrtf(ss / (float)p.K + p.eps);
 }
+// the same by a wave whose lanes hold slots t, increasing by lane (all lanes on)
 __device__ __forceinline__ float row_rstd(const GemmP& p, int t) {
     if (p.nss == nullptr) return 1.0f;
     float ss = 0.f;
-    for (int b = 0; b < p.nnb; ++b) ss += p.nss[(size_t)t * p.nnb + b];
+    if (p.nnb <= kNormKMax / kNormBlock) {
+        for (int b = 0; b < p.nnb; ++b) ss += p.nss[(size_t)t * p.nnb + b];
+    } else {
+        // a few-slot product's sums, one per few columns: lanes over the blocks
+        // of each slot of the wave (every thread walking them: +14 us a layer at
+        // 256 blocks)
+        const int last = __shfl(t, 63, 64);
+        for (int r = __builtin_amdgcn_readfirstlane(t); r <= last; ++r) {
+            const float v = lane_blocks_sum(p.nss + (size_t)r * p.nnb, p.nnb, threadIdx.x & 63);
+            if (r == t) ss = v;
+        }
+    }
     return 1.0f / sqrtf(ss / (float)p.K + p.eps);
 }
 // block sums that do not fit a thread's registers (the few-slot products
@@ -1265,9 +1277,10 @@ template <int EPI>
 __global__ __launch_bounds__(256) void k_splitk_reduce(GemmP p) {
     const int ncols = EPI == EPI_SWIGLU ? p.vcols / 2 : p.vcols;
     const int per_row = ncols / 4;
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx >= p.T * per_row) return;
+    const int all = p.T * per_row, idx = min((int)(blockIdx.x * 256 + threadIdx.x), all - 1);
     const int t = idx / per_row, c = (idx % per_row) * 4;
+    const float sc = row_rstd(p, t);
+    if ((int)(blockIdx.x * 256 + threadIdx.x) >= all) return;
     const size_t stride = (size_t)p.T * p.vcols;
     const float* base = p.part + (size_t)t * p.vcols;
     if (EPI == EPI_SWIGLU) {
@@ -1277,11 +1290,11 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(GemmP p) {
             g += *(const f32x4*)(base + s * stride + vg);
             u += *(const f32x4*)(base + s * stride + vg + 16);
         }
-        swiglu_store4(p, t, c, g, u, row_rstd(p, t));
+        swiglu_store4(p, t, c, g, u, sc);
     } else {
         f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
         for (int s = 0; s < p.S; ++s) v += *(const f32x4*)(base + s * stride + c);
-        epi_store4(p, t, c, v, row_rstd(p, t));
+        epi_store4(p, t, c, v, sc);
     }
 }
 
