@@ -1430,8 +1430,6 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmF p) {
 // split policy, see choose_splits.
 struct GemmShape { int F, MT, NW, CS, NG, KC, UR, FILL; };
 
-static int cu_count();
-
 // The 16x16 form (four-wave workgroups of 128 weight rows, 64-k chunks) serves
 // products up to 96 slots that are too small to fill the GPU with 256-row
 // workgroups of enough k each; the 32x32 form serves everything else, with
@@ -1555,7 +1553,7 @@ static ReduceFn pick_reduce(int epi) {
     }
 }
 
-static int cu_count() {  // cached
+int cu_count() {  // cached
     static int n = 0;
     if (n == 0) {
         int dev = 0;

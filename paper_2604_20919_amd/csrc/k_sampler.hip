@@ -473,10 +473,11 @@ void launch_sampler(const Dims& D, const BatchView& bv, const SlotBufs& sb, cons
     if (groups > 0) {
         hipLaunchKernelGGL(k_samp_a2<true>, dim3(bv.T), dim3(256), 0, s, p, chunks);
     } else {
-        // phase A chunks: about 4096 workgroups in all (each pays its merge,
+        // phase A chunks: about 16 workgroups a CU in all (each pays its merge,
         // 64 chunks a slot cost 32 us for 108 slots of 151936 against 15),
         // at least one 4096-element tile each
-        const int ca = std::max(1, std::min(std::min(kVocabChunks, (4096 + bv.T - 1) / bv.T), (D.V + 4095) / 4096));
+        const int wgs = 16 * cu_count();
+        const int ca = std::max(1, std::min(std::min(kVocabChunks, (wgs + bv.T - 1) / bv.T), (D.V + 4095) / 4096));
         p.cwa = ((D.V + ca - 1) / ca + 3) & ~3;
         p.chunks_a = (D.V + p.cwa - 1) / p.cwa;
         const dim3 ga(bv.T, p.chunks_a);
@@ -489,7 +490,7 @@ void launch_sampler(const Dims& D, const BatchView& bv, const SlotBufs& sb, cons
     if (bv.mode == 1) {
         // whole waves, as many as are resident at once over all users (24 a
         // CU), each thread taking the same number of four-element tiles
-        const int quads = p.cw / 4, most = std::min(16, std::max(1, 24 * 256 / (bv.B * chunks))) * 64;
+        const int quads = p.cw / 4, most = std::min(16, std::max(1, 24 * cu_count() / (bv.B * chunks))) * 64;
         const int tiles = (quads + most - 1) / most;
         const int nt = ((quads + tiles - 1) / tiles + 63) & ~63;
         if (bv.qk > 0)

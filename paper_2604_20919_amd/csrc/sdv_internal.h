@@ -170,6 +170,8 @@ constexpr int kSkPollsDefault = 1 << 18;
 // Upper bound of the statistic groups of an lm_head of V rows (workgroups
 // of at least 128 rows, one more for rounding)
 inline int lm_stat_groups_max(int V) { return (V + 127) / 128 + 1; }
+// Compute units of the current device
+int cu_count();
 // Returns the number of partial planes S (raw mode; negative: the residual
 // step is done, see res_gamma), else the splits used.
 int launch_gemm(const Dims& D, const GemmCall& g, const SlotBufs& sb, hipStream_t s);
