@@ -224,36 +224,37 @@ __device__ __forceinline__ void store_partial_rows(const GemmP& p, const float* 
     }
 }
 
-// 16x16x32 form.  MT: 16-slot tiles; NSUB: 16-row weight groups per wave;
-// KC: k per chunk (a multiple of 32); NW: waves per workgroup; PL:
-// activation planes; PD: chunks of prefetch.
-// XPAD: bf16 elements of padding per staged row.  With 16 (a row stride of
-// an odd multiple of 32 bytes) the B-fragment reads of 32 lanes (16 rows at
-// two k offsets) hit distinct banks of the 128-bank LDS, and the staging
-// stores are ordered so that the rows written together sit 16/R rows apart
-// (R rows per 32 lanes), which also spreads them over every bank.  With 8
-// (stride 272 or 144 bytes) rows 0 and 15 of a read share banks.
-// LA (split SwiGLU product reduced by its last split): the S workgroups of
-// a row tile each take a k range, store their sums and count themselves;
-// the one that counts last adds every split's sums in split order and
-// runs the SwiGLU epilogue, so no separate reduction kernel is needed.
-template <int MT, int NSUB, int KC, int EPI, bool SPLIT, int NW, int PL, int PD, int XPAD = 16, bool LA = false>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, 2)))
+// 16x16x32 form.  MT: 16-slot tiles.  Staged rows are padded to a stride of an
+// odd multiple of 32 bytes: the B-fragment reads of 32 lanes (16 rows at two k
+// offsets) then hit distinct banks of the 128-bank LDS, and the staging stores
+// are ordered so that the rows written together sit 16/R rows apart (R rows
+// per 32 lanes), which also spreads them over every bank.
+// The SwiGLU product is always split and reduced by its last split: the S
+// workgroups of a row tile each take a k range, store their sums and count
+// themselves; the one that counts last adds every split's sums in split order
+// and runs the epilogue, so no separate reduction kernel is needed.
+template <int MT, int EPI, bool SPLIT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2)))
 void k_gemm16(GemmP p) {
+    constexpr int NW = 4;                // waves per workgroup
     constexpr int NTH = 64 * NW;         // threads per workgroup
+    constexpr int NSUB = 2;              // 16-row weight groups per wave (SwiGLU: a gate/up pair)
+    constexpr int PL = 2;                // activation planes
+    constexpr int PD = 2;                // chunks of prefetch
+    constexpr int KC = 64;               // k per chunk
+    constexpr bool LA = EPI == EPI_SWIGLU;
     constexpr int ROWS_PER_TILE = 16;
     constexpr int KS = KC / 32;          // MFMA k-steps per chunk
-    constexpr int LDX = KC + XPAD;       // padded LDS row (bf16 elements)
+    constexpr int LDX = KC + 16;         // padded LDS row (bf16 elements)
     constexpr int PPR = KC / 8;          // 16-byte pieces per staged row
-    constexpr int RPP = PPR >= 32 ? 1 : 32 / PPR;  // staged rows per 32 lanes
+    constexpr int RPP = 32 / PPR;        // staged rows per 32 lanes
     constexpr int NPP = MT * 16 * PPR;   // pieces per staged plane
     constexpr int NPC = PL * NPP;        // pieces per staged chunk (all planes)
-    constexpr int XPT = (NPC + NTH - 1) / NTH;  // X pieces per thread
-    constexpr bool XEVEN = NPC % NTH == 0;
+    constexpr int XPT = NPC / NTH;       // X pieces per thread
     constexpr int PLANE = MT * 16 * LDX;  // LDS elements per plane
-    static_assert(EPI != EPI_SWIGLU || NSUB % 2 == 0, "SwiGLU pairs gate/up sub-tiles");
+    static_assert(NPC % NTH == 0, "whole X pieces per thread");
     static_assert(2 * PL * PLANE * 2 <= 160 * 1024, "X staging exceeds LDS");
-    static_assert(!LA || (!SPLIT && EPI == EPI_SWIGLU), "last-split reduction: the SwiGLU product");
+    static_assert(!LA || !SPLIT, "last-split reduction: no partial planes");
     __shared__ __attribute__((aligned(16))) bf16_t xs[2][PL * PLANE];
     __shared__ float rsl[SPLIT ? 1 : MT * ROWS_PER_TILE];  // per-slot RMSNorm factor
     __shared__ int la_count;  // LA: splits of this tile counted before this one
@@ -309,15 +310,11 @@ void k_gemm16(GemmP p) {
     uint4 xr[NB][XPT];
     bf16x8 wr[NB][KS][NSUB];
     uint32_t xoff[XPT];
-    // staging order q -> LDS row (a permutation within each block of 16
-    // rows; the identity for XPAD != 16)
-    auto staged_row = [](int q) {
-        if constexpr (XPAD != 16 || RPP == 1) return q;
-        else return (q & ~15) | ((q % RPP) * (16 / RPP)) | ((q / RPP) % (16 / RPP));
-    };
+    // staging order q -> LDS row (a permutation within each block of 16 rows)
+    auto staged_row = [](int q) { return (q & ~15) | ((q % RPP) * (16 / RPP)) | ((q / RPP) % (16 / RPP)); };
 #pragma unroll
     for (int i = 0; i < XPT; ++i) {
-        const int idx = min((int)threadIdx.x + i * NTH, NPC - 1);
+        const int idx = (int)threadIdx.x + i * NTH;
         const int pl = idx / NPP, pi = idx % NPP;
         const int r = min(staged_row(pi / PPR), p.T - 1), cc = pi % PPR;
         xoff[i] = (((uint32_t)pl * (uint32_t)p.T + (uint32_t)r) * (uint32_t)p.K + (uint32_t)cc * 8u) * 2u;
@@ -333,8 +330,7 @@ void k_gemm16(GemmP p) {
         for (int i = 0; i < XPT; ++i) {
             const int idx = threadIdx.x + i * NTH;
             const int pl = idx / NPP, pi = idx % NPP;
-            if (XEVEN || idx < NPC)
-                *(uint4*)(&xs[buf][pl * PLANE + staged_row(pi / PPR) * LDX + (pi % PPR) * 8]) = x[i];
+            *(uint4*)(&xs[buf][pl * PLANE + staged_row(pi / PPR) * LDX + (pi % PPR) * 8]) = x[i];
         }
     };
     auto load_w = [&](bf16x8 (&w)[KS][NSUB], int c) {
@@ -1485,12 +1481,8 @@ typedef void (*ReduceFn)(GemmP);
 // partial planes and the epilogue runs in the reducer.
 template <int MT>
 static GemmFn pick16(bool split, int epi) {
-    if (split) return k_gemm16<MT, 2, 64, EPI_STORE, true, 4, 2, 2>;
-    switch (epi) {
-        case EPI_SWIGLU: return k_gemm16<MT, 2, 64, EPI_SWIGLU, false, 4, 2, 2>;
-        case EPI_LMSTAT: return k_gemm16<MT, 2, 64, EPI_LMSTAT, false, 4, 2, 2>;
-        default: return k_gemm16<MT, 2, 64, EPI_STORE, false, 4, 2, 2>;
-    }
+    if (split) return k_gemm16<MT, EPI_STORE, true>;
+    return epi == EPI_LMSTAT ? k_gemm16<MT, EPI_LMSTAT, false> : k_gemm16<MT, EPI_STORE, false>;
 }
 
 template <int MT, int CS>
@@ -1532,16 +1524,16 @@ static GemmFn pick(const GemmShape& sh, bool split, int epi, int sk = SK_NONE) {
     }
 }
 
-// the last-split SwiGLU product on the 16x16 tiles
+// the last-split SwiGLU product on the 16x16 tiles (17-96 slots: products this
+// small are the few-slot form's up to 16)
 static GemmFn pick_la(const GemmShape& sh) {
     if (sh.F != 16) return nullptr;
     switch (sh.MT) {
-        case 1: return k_gemm16<1, 2, 64, EPI_SWIGLU, false, 4, 2, 2, 16, true>;
-        case 2: return k_gemm16<2, 2, 64, EPI_SWIGLU, false, 4, 2, 2, 16, true>;
-        case 3: return k_gemm16<3, 2, 64, EPI_SWIGLU, false, 4, 2, 2, 16, true>;
-        case 4: return k_gemm16<4, 2, 64, EPI_SWIGLU, false, 4, 2, 2, 16, true>;
-        case 5: return k_gemm16<5, 2, 64, EPI_SWIGLU, false, 4, 2, 2, 16, true>;
-        case 6: return k_gemm16<6, 2, 64, EPI_SWIGLU, false, 4, 2, 2, 16, true>;
+        case 2: return k_gemm16<2, EPI_SWIGLU, false>;
+        case 3: return k_gemm16<3, EPI_SWIGLU, false>;
+        case 4: return k_gemm16<4, EPI_SWIGLU, false>;
+        case 5: return k_gemm16<5, EPI_SWIGLU, false>;
+        case 6: return k_gemm16<6, EPI_SWIGLU, false>;
     }
     return nullptr;
 }
@@ -1708,6 +1700,9 @@ int launch_gemm(const Dims& D, const GemmCall& g, const SlotBufs& sb, hipStream_
     // 14.3 -> 14.0 us per layer; the down projection, k = 6144, is slower
     // so: 19.4 -> 20.0 us)
     if (g.raw && sh.F == 16 && sh.FILL && g.K <= 2048) S = std::max(1, S / 2);
+    // (the 16x16 SwiGLU form is a split one; its row tiles are fewer than half
+    // the CUs and k at least four chunks, so that there are two anyway)
+    if (sh.F == 16 && g.epi == EPI_SWIGLU) S = std::max(S, 2);
     while (S > 1 && (size_t)S * g.T * p.vcols > sb.gpart_floats) {
         int t = S - 1;
         while (t > 1 && p.kchunks % t) --t;
