@@ -18,8 +18,10 @@
 //     buffered) and read by all waves of the workgroup as the B operand;
 //     activations come as two bf16 planes (hi, lo = x - hi) that are
 //     multiplied separately, which carries them at about 16 significant bits;
-//   * each wave owns a fixed set of weight rows and all T slots, so every
-//     weight byte is read once per call;
+//   * a wave owns a fixed set of weight rows and multiplies every slot of its
+//     workgroup with them, so a weight byte leaves HBM once per call (from six
+//     slot tiles on two waves share the rows, above 256 slots two workgroups of
+//     one XCD, the second finding them in its L2);
 //   * when there are too few column tiles to fill the GPU the k range is
 //     split over S workgroups; partial sums are written to a workspace and a
 //     second kernel (or a fused consumer) adds them in split order and
@@ -547,7 +549,7 @@ __device__ __forceinline__ void lds_read_tiles(bf16x8 (&f)[N], uint32_t a) {
     if constexpr (N == 3)
         asm volatile("ds_read_b128 %0, %3\n\tds_read_b128 %1, %3 offset:4096\n\tds_read_b128 %2, %3 offset:8192"
                      : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]) : "v"(a) : "memory");
-    static_assert(N >= 1 && N <= 6, "tiles per wave");
+    static_assert(N >= 1 && N <= 5, "tiles per wave");
     if constexpr (N == 4)
         asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:4096\n\tds_read_b128 %2, %4 offset:8192\n\t"
                      "ds_read_b128 %3, %4 offset:12288"
@@ -556,12 +558,6 @@ __device__ __forceinline__ void lds_read_tiles(bf16x8 (&f)[N], uint32_t a) {
         asm volatile("ds_read_b128 %0, %5\n\tds_read_b128 %1, %5 offset:4096\n\tds_read_b128 %2, %5 offset:8192\n\t"
                      "ds_read_b128 %3, %5 offset:12288\n\tds_read_b128 %4, %5 offset:16384"
                      : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]) : "v"(a) : "memory");
-    if constexpr (N == 6)
-        asm volatile("ds_read_b128 %0, %6\n\tds_read_b128 %1, %6 offset:4096\n\tds_read_b128 %2, %6 offset:8192\n\t"
-                     "ds_read_b128 %3, %6 offset:12288\n\tds_read_b128 %4, %6 offset:16384\n\t"
-                     "ds_read_b128 %5, %6 offset:20480"
-                     : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]), "=&v"(f[5])
-                     : "v"(a) : "memory");
 }
 template <int LEFT, int N>
 __device__ __forceinline__ void lds_wait_tiles(bf16x8 (&f)[N]) {
@@ -573,16 +569,13 @@ __device__ __forceinline__ void lds_wait_tiles(bf16x8 (&f)[N]) {
     if constexpr (N == 5)
         asm volatile("s_waitcnt lgkmcnt(%5)"
                      : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]) : "n"(LEFT));
-    if constexpr (N == 6)
-        asm volatile("s_waitcnt lgkmcnt(%6)"
-                     : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]), "+v"(f[5]) : "n"(LEFT));
 }
 
 // 32x32x16 form.  MT: 32-slot tiles of a workgroup; a wave multiplies 64
 // weight rows (two 32-row groups), so every B fragment read from LDS feeds two
 // MFMAs: four SIMDs issuing 32-cycle MFMAs then ask for 64 bytes per clock of
 // LDS reads instead of 128.
-// CS = 1, four waves (up to six tiles, one set of accumulators per wave; up
+// CS = 1, four waves (up to five tiles, one set of accumulators per wave; up
 // to four tiles two workgroups share a CU); CS = 2 (column split), eight
 // waves: two waves share one row unit and each multiplies MT/2 of the tiles.
 // Both hold 256 weight rows per workgroup.
@@ -750,10 +743,11 @@ void k_gemm32(GemmP p) {
             load_row_ss(p, min(tb + sl, p.T - 1), p.nss != nullptr && sl < NSL, ssv[i]);
         }
     }
-    // Packed last tile (when the group's last tile holds at most 16 slots):
-    // its rows 0-15 hold their hi plane and rows 16-31 their lo plane, one
-    // tile-plane instead of two; the wave that holds it multiplies it in the
-    // plane-0 phases only
+    // Packed last tile (when the last tile holds at most 16 slots): its rows
+    // 0-15 hold their hi plane and rows 16-31 their lo plane, one tile-plane
+    // instead of two; the wave that holds it multiplies it in the plane-0
+    // phases only.  Not with slot groups, where every slot's sums are one chain
+    // (359 slots: 1% of the products' time)
     const int last_n = p.T - tb - (MT - 1) * 32;
     const bool pkl = p.ng == 1 && last_n > 0 && last_n <= 16;
     const bool pkl_half = pkl && half == CS - 1;
@@ -1433,8 +1427,8 @@ struct GemmShape { int F, MT, NW, CS, NG, KC, UR, FILL; };
 // replaced (one machine, Qwen3-32B shapes, us): T = 16 gate/up 80.0 -> 79.6,
 // lm_head 279 -> 270; T = 60 100 -> 96, 328 -> 308; T = 96 156 -> 125, 470 -> 352,
 // the three projections together 129 -> 101 on average of three; T = 128 175 -> 157,
-// 534 -> 424; T = 160 202 -> 175; T = 192 229 -> 194; T = 224 275 -> 242; T = 300
-// (13-tile four-wave tiles with 16-k chunks before) 650 -> 344; T = 384 715 -> 390.
+// 534 -> 424; T = 160 202 -> 159; T = 192 229 -> 181; T = 224 275 -> 217; T = 300
+// (13-tile four-wave tiles with 16-k chunks before) 650 -> 274; T = 384 715 -> 316.
 static GemmShape shape_for(int T, int vcols, bool raw, int K) {
     const bool wide = vcols % 256 == 0;
     constexpr int kT32 = 97;  // slot counts the 16x16 form's tiles end at
@@ -1464,14 +1458,15 @@ static GemmShape shape_for(int T, int vcols, bool raw, int K) {
     auto s32 = [](int MT, int CS, int NG) { return GemmShape{32, MT, 4 * CS, CS, NG, 64, 64, 1}; };
     if (mt <= 5) return s32(mt, 1, 1);
     // six tiles and up: the column split is faster than four waves with all
-    // tiles (T = 384 in two groups of six: gate/up 390 against 410 us)
+    // tiles (T = 384 in two groups of six, measured with a tile's pieces added
+    // up: gate/up 390 against 410 us)
     if (mt == 6) return s32(6, 2, 1);
     if (mt <= 8) return s32(8, 2, 1);
     // two slot groups; five tiles do not halve, so they take four waves
-    // (T = 300: gate/up 344 us against 378 for two groups of six)
+    // (T = 300: gate/up 274 us against 311 for two groups of six)
     if (mt <= 10) return s32(5, 1, 2);
     if (mt <= 12) return s32(6, 2, 2);
-    return s32(8, 2, 2);  // three groups of five: 502 against 485 us at T = 400
+    return s32(8, 2, 2);  // three groups of five: 418 against 394 us at T = 400
 }
 
 typedef void (*GemmFn)(GemmP);
@@ -1602,8 +1597,8 @@ size_t gemm_partial_floats(const Dims& D, int Tmax) {
 // (14 slots: gate/up 16.2 -> 15.5 us; the others 8.2-15.6 against 7.5-9.9.)
 // The workgroups must all be resident at once (two eight-wave ones or one
 // sixteen-wave one per CU): with more (the Qwen3-32B projections) the tiled
-// forms' split k is faster (8 slots, 16 layers: 3370 against 3900 us).  Returns 0 when another form takes the call, else
-// the columns of a workgroup.
+// forms' split k is faster (8 slots, 16 layers: 3370 against 3900 us).  Returns
+// 0 when another form takes the call, else the columns of a workgroup.
 static int try_few(const Dims& D, const GemmCall& g, const SlotBufs& sb, hipStream_t s) {
     const bool swiglu = g.epi == EPI_SWIGLU;
     if (g.T > (swiglu ? 16 : 8) || g.K % 128 || g.N % 16 || g.epi == EPI_LMSTAT) return 0;
