@@ -1730,8 +1730,8 @@ int launch_gemm(const Dims& D, const GemmCall& g, const SlotBufs& sb, hipStream_
     p.sk_polls = g.sk_polls;
     p.sk_cnt = g.sk_cnt;
     p.flags = g.flags;
-    if (!g.raw && g.epi == EPI_SWIGLU && sh.F == 32 && sh.MT == 8 && sh.NG == 1 && g.T > 224 && S == 1 && g.sk_cnt && g.flags &&
-        p.tiles < cu_count() && p.tiles <= kSkCounters) {
+    if (!g.raw && g.epi == EPI_SWIGLU && sh.F == 32 && sh.MT == 8 && sh.NG == 1 && g.T > 224 && S == 1 &&
+        g.sk_cnt && g.flags && p.tiles < cu_count() && p.tiles <= kSkCounters) {
         const int total = p.tiles * p.kchunks, nwg = std::min(cu_count(), total);
         int maxp = 0;  // most pieces of a tile before its last
         for (int t = 0; t < p.tiles; ++t)

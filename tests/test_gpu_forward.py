@@ -225,14 +225,12 @@ def _ragged_draft_lengths(T_target, rng):
 @pytest.mark.parametrize("T_target", [17, 64, 65, 70, 75, 80, 96, 97, 105, 112, 113, 120, 128, 129, 150, 224, 225,
                                       232, 240, 241, 250, 256, 257, 300, 320, 321, 416])
 def test_bf16_every_gemm_tile_class(T_target):
-    """Query-slot totals that select each GEMM tile class, and both sides of
-    every boundary between them: the 16x16 form up to 96 slots, the 32x32
-    form above (eight-wave tiles up to 256 slots, four-wave tiles above;
-    32-k chunks at 225..320 slots, 16-k chunks above 320; at 225..240 the
-    last slot tile holds both planes of its 16 slots), the
-    packed-plane 32x32 tiles (split-K partials at 65..80 slots, every GEMM
-    at 97..112, with and without padding in the mixed tile), split-K and
-    unsplit paths, up to the 416-slot maximum."""
+    """Query-slot totals around every boundary between the GEMM tile classes of
+    the toy model: the 16x16 form up to 96 slots, the 32x32 form above (four
+    and five 32-slot tiles on four waves, six and eight on eight, two slot
+    groups above 256 slots; up to 256 a last tile of at most 16 slots holds
+    both their planes), split-K and unsplit paths, up to the 416-slot
+    maximum."""
     rng = np.random.default_rng(T_target)
     L = _ragged_draft_lengths(T_target, rng)
     prefix = [int(p) for p in rng.integers(0, 200, size=len(L))]
@@ -283,10 +281,10 @@ def test_last_split_gate_up_repeats_and_never_waits(T_target):
 @pytest.mark.parametrize("T_target", [40, 120])
 def test_split_gate_up_with_reduction_kernel(T_target):
     """A gate/up product of 96 row tiles of 256 rows (a 12288-wide
-    feed-forward layer) below 225 slots is split over k in two, and a
-    separate kernel adds the halves and applies SwiGLU: the form for
-    products too wide for the four-wave tiles and too narrow to fill the
-    CUs unsplit.  Parity with the oracle."""
+    feed-forward layer) is split over k in two, and a separate kernel adds
+    the halves and applies SwiGLU: the form for products too wide for the
+    16x16 tiles and too narrow to fill the CUs unsplit.  Parity with the
+    oracle."""
     rng = np.random.default_rng(300 + T_target)
     L = _ragged_draft_lengths(T_target, rng)
     prefix = [int(p) for p in rng.integers(0, 300, size=len(L))]

@@ -1,19 +1,19 @@
 """Parity at the benchmark sizes.
 
 The Qwen3-32B-shaped workloads (16-user batch, 32-user ragged batch, four
-pipelined 16-user batches, plus batches at 40, 88 and 132 slots) run through
+pipelined 16-user batches, plus batches at 40, 88, 132 and 359 slots) run through
 the C ABI exactly as the benchmark runs them, and the oracle recomputes
 users one by one (users are independent, so a user's logits and decisions
 do not depend on the rest of its batch):
   * the 16-user batch: every user, in stochastic and in greedy mode;
-  * ragged batches: for every GEMM slot tile (16 slots below 97, 32 above)
-    the user holding its first slot, plus the users with the shortest and
-    the longest context (one attention chunk against several) and the most
-    drafts;
-  * the pipelined batches: in the first batch (97..112 slots: packed
-    planes, a partly filled last slot tile) the user with most slots and
-    the one holding the last slot; in the last the one with the longest
-    prefix.
+  * ragged batches: at every 16th slot below 97 slots, every 32nd (a GEMM
+    slot tile) above, the user holding it, plus the users with the shortest
+    and the longest context (one attention chunk against several) and the
+    most drafts; above 256 slots the users holding the first slot of either
+    slot group and the last slot;
+  * the pipelined batches: in the first batch (four slot tiles, the last
+    partly filled) the user with most slots and the one holding the last
+    slot; in the last the one with the longest prefix.
 All 32B workloads are drawn with one seed (their shapes and distributions
 are the benchmark's; the draws differ from the benchmark's own seeds) so
 that the host generates the 64 layers once for the oracle.  The
@@ -36,10 +36,9 @@ pytestmark = pytest.mark.gpu
 
 SEED32 = 3  # the seed of the 16-user workload; shared by every 32B workload here
 WORKLOADS32 = ("qwen3-32b-b16", "qwen3-32b-ragged32", "qwen3-32b-pipe4x16")
-# Batches of the 32B shape at 40 and 88 slots: there its QKV, O and down
-# projections run on eight-wave 16x16 split-K tiles, which neither the
-# benchmark workloads (80, 97..132 and 229 slots) nor the smaller models
-# (whose narrow matrices take four-wave tiles) reach.  (prefix lengths,
+# Batches of the 32B shape at slot counts that the benchmark workloads (80,
+# 97..132 and 229 slots) do not reach, where its products run on other slot
+# tiles: two tiles (40), a third that is nearly full (88).  (prefix lengths,
 # draft lengths)
 CUSTOM32 = {
     "qwen3-32b-t40": ([100 + 37 * i for i in range(8)], [4] * 8),
@@ -47,6 +46,8 @@ CUSTOM32 = {
     # five 32-slot tiles of the 32x32 form (129..160 slots), which the
     # pipelined batches reach with the benchmark's draws
     "qwen3-32b-t132": ([64 + 23 * i for i in range(16)], [7] * 12 + [8] * 4),
+    # two slot groups of six tiles (321..384 slots), seven slots in the last tile
+    "qwen3-32b-t359": ([40 + 5 * i for i in range(33)], [10] * 32 + [6]),
 }
 MODES32 = {"qwen3-32b-b16": ("stochastic", "greedy")}
 TOL = 2e-2
@@ -75,8 +76,10 @@ def _pick(w: wl.Workload, n: int, b: wl.Batch):
         return [int(np.argmax(b.prefix_len))] if n == w.n_batches - 1 else []
     if np.all(b.draft_len == b.draft_len[0]) and np.all(b.prefix_len == b.prefix_len[0]):
         return list(range(len(b.users)))
-    tile = 16 if b.T < 97 else 32
     so = np.concatenate([[0], np.cumsum(b.n_slots)])
+    if b.T > 256:
+        return sorted({int(np.searchsorted(so, t0, side="right") - 1) for t0 in (0, 192, b.T - 1)})
+    tile = 16 if b.T < 97 else 32
     first = [int(np.searchsorted(so, t0, side="right") - 1) for t0 in range(0, b.T, tile)]
     ctx = b.prefix_len + b.n_slots
     return sorted(set(first) | {int(np.argmin(ctx)), int(np.argmax(ctx)), int(np.argmax(b.draft_len))})

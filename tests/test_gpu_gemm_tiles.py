@@ -3,8 +3,8 @@ oracle: one to six 32-slot tiles on four waves, six and eight on eight, two
 slot groups above 256 slots; both sides of every boundary, and last tiles that
 hold at most 16 slots (both planes in one tile) next to ones that hold more.
 
-tiny-wide-ffn: 160 gate/up row tiles, unsplit up to 128 slots and split over
-every CU above (at two slot groups a workgroup takes up to three pieces).
+tiny-wide-ffn: 160 gate/up row tiles, unsplit up to 224 slots, split over every
+CU at 225-256 and, at two slot groups, shared out over every CU.
 tiny-deep-ffn: a down projection of four row tiles over a k of 16384, split
 64 ways (the split-K form at small slot counts), and 128 gate/up row tiles
 split in two with a reduction kernel.

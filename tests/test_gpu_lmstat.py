@@ -7,9 +7,9 @@ race reads them; SD_LOGITS_UNFUSED stores every slot's logits and computes
 the statistics from them by separate kernels.  On the Qwen3-1.7B shape
 (vocabulary 151936) both contexts, given the same weights and inputs, must
 agree bit for bit: accepted counts and tokens in all three modes, at slot
-counts of every lm_head tile class (16-slot tiles below 97 slots, 32-slot
-tiles of four-wave and eight-wave workgroups, ten and thirteen 32-slot
-tiles), and the stored logits wherever both store them."""
+counts of every kind of lm_head tile (16-slot tiles below 97 slots, 32-slot
+tiles of four-wave and eight-wave workgroups, two slot groups of five and
+of eight 32-slot tiles), and the stored logits wherever both store them."""
 import numpy as np
 import pytest
 import torch
