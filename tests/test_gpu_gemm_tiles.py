@@ -1,5 +1,5 @@
 """Every tile shape of the 32x32 GEMM form on toy bf16 models, against the
-oracle: one to six 32-slot tiles on four waves, six and eight on eight, two
+oracle: one to five 32-slot tiles on four waves, six and eight on eight, two
 slot groups above 256 slots; both sides of every boundary, and last tiles that
 hold at most 16 slots (both planes in one tile) next to ones that hold more.
 
